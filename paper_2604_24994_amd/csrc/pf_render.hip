@@ -8,11 +8,13 @@
 //   scan/scatter  counting sort by tile
 //   k_tile_sort   per tile, sort by (key, cell) in LDS (bitonic, global
 //                 memory fallback for long lists)
+//   k_split_plan  which tiles go to which of the two composites
 //   k_raster      one 256-thread workgroup per 16x16 tile, one lane per
 //                 pixel, each wave an 8x8 quadrant walking the tile's list
 //                 front to back; the list and the cells' records are staged
-//                 in LDS 256 entries at a time by the whole workgroup, so a
-//                 cell that misses the quadrant costs no memory latency
+//                 in LDS 256 entries at a time by the whole workgroup, and
+//                 cells that miss the quadrant are dropped 64 at a time
+//   k_raster_split  tiles with long lists: sixteen waves per 8x8 quadrant
 // Trace, per view (Sec. 3.2, ray tracing; appendix C):
 //   k_start_*     argmin power distance from the camera centre
 //   k_trace       one lane per ray; per step the piece of the current cell
@@ -416,18 +418,349 @@ __device__ inline void tile_pixel(int tiles_x, int& px, int& py, int tile = -1) 
   py = ty * TILE + (w >> 1) * 8 + (lane >> 3);
 }
 
+// Record buffers of a store-mode pass and the slots a wave holds of them.
+struct RecOut {
+  int4* ri;
+  float4* rf;
+  float* rt;
+  unsigned long long* counter;
+  int4* seg;
+  int64_t cap, seg_cap;
+};
+
+struct WaveSlots {
+  long long rblk = 0, sblk = 0;   // next slots of the current record / segment block
+  long long cblk = -1;            // first slot (header) of the current segment block
+  int rleft = 0, sleft = 0;
+};
+
+// Appends the records of the lanes in m (one cell's contributions over the
+// wave's pixels, all lanes active): slots come from the wave's own blocks; a
+// new block is reserved with one global atomic when the current one cannot
+// take the append.
+__device__ inline void append_records(const RecOut& O, WaveSlots& W, uint64_t m, int lane, uint64_t lt, int ci, int pix,
+                                      int view_bind, float alpha, float r, float g, float b, float T, int& head) {
+  const int cnt = __popcll(m);
+  if (cnt > W.rleft) {
+    unsigned long long bk = 0;
+    if (lane == 0) bk = atomicAdd(&O.counter[0], (unsigned long long)RBLK);
+    W.rblk = (long long)bcast64(bk);
+    W.rleft = RBLK;
+  }
+  if (W.sleft == 0) {
+    unsigned long long bk = 0;
+    if (lane == 0) bk = atomicAdd(&O.counter[1], (unsigned long long)SBLK);
+    const long long nb = (long long)bcast64(bk);
+    // the block's header links it to the wave's previous block
+    if (lane == 0 && nb < O.seg_cap) O.seg[nb] = make_int4(-1, (int)W.cblk, 0, 0);
+    W.cblk = nb;
+    W.sblk = nb + 1;
+    W.sleft = SBLK - 1;
+  }
+  const long long base = W.rblk, sg = W.sblk;
+  W.rblk += cnt;
+  W.rleft -= cnt;
+  W.sblk += 1;
+  W.sleft -= 1;
+  if (lane == 0 && sg < O.seg_cap && base + cnt <= O.cap)
+    O.seg[sg] = make_int4(ci, (int)base, (int)(uint32_t)m, (int)(uint32_t)(m >> 32));
+  if ((m >> lane) & 1ull) {
+    const long long slot = base + __popcll(m & lt);
+    if (slot < O.cap) {
+      O.ri[slot] = make_int4(ci, pix, head, view_bind);
+      O.rf[slot] = make_float4(alpha, r, g, b);
+      O.rt[slot] = T;
+      head = (int)slot;
+    }
+  }
+}
+
+// Ends a wave's segment list: unused slots of its last block are marked
+// empty (mask 0); *tail receives the block and the slots used in it.
+__device__ inline void close_segments(const RecOut& O, const WaveSlots& W, int lane, int2* tail) {
+  for (int j = lane; j < W.sleft; j += 64)
+    if (W.sblk + j < O.seg_cap) O.seg[W.sblk + j] = make_int4(0, 0, 0, 0);
+  if (lane == 0) *tail = make_int2((int)W.cblk, SBLK - W.sleft);
+}
+
+// View of a tile of the group: the last one whose tiles start at or before it.
+__device__ inline const ViewDev& tile_view(const ViewDev* __restrict__ views, int nview, int64_t gtile) {
+  int lo = 0, hi = nview - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (views[mid].tile_base <= (long long)gtile) lo = mid; else hi = mid - 1;
+  }
+  return views[lo];
+}
+
+__device__ inline float wave_min_f(float x) {
+  for (int o = 32; o > 0; o >>= 1) x = fminf(x, __shfl_xor(x, o, 64));
+  return x;
+}
+__device__ inline float wave_add_f(float x) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+// Cone around the rays of a wave's 8x8 pixels (camera centre o, unit axis a,
+// half-angle with cosine ct and sine st).  A cell's ball can only be met by
+// one of those rays if it reaches the cone, which ray_cone_meets tests for
+// 64 cells at a time, one per lane; the exact per-pixel test follows for
+// the cells that pass, so the test only has to err on the side of passing.
+struct RayCone {
+  float ox, oy, oz, ax, ay, az, ct, st;
+};
+
+__device__ inline RayCone ray_cone(const RayD& R, bool use) {
+  RayCone C;
+  C.ox = (float)R.ox;   // (float32 values)
+  C.oy = (float)R.oy;
+  C.oz = (float)R.oz;
+  const float sx = wave_add_f(use ? R.fx : 0.0f), sy = wave_add_f(use ? R.fy : 0.0f),
+              sz = wave_add_f(use ? R.fz : 0.0f);
+  const float n2 = sx * sx + sy * sy + sz * sz;
+  const float inv = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
+  C.ax = sx * inv;
+  C.ay = sy * inv;
+  C.az = sz * inv;
+  // sine of the largest angle to a ray, from the cross product (accurate for
+  // small angles), a little widened
+  const float ux = C.ay * R.fz - C.az * R.fy, uy = C.az * R.fx - C.ax * R.fz, uz = C.ax * R.fy - C.ay * R.fx;
+  const float s2 = -wave_min_f(use ? -(ux * ux + uy * uy + uz * uz) : 0.0f);
+  const float dmin = wave_min_f(use ? C.ax * R.fx + C.ay * R.fy + C.az * R.fz : 1.0f);
+  // a cone of more than about 60 degrees (images of a few pixels) is not used
+  const bool ok = dmin > 0.5f && inv > 0.0f;
+  C.st = ok ? sqrtf(s2) * (1.0f + 1e-4f) + 2e-6f : 2.0f;
+  C.ct = ok ? sqrtf(fmaxf(0.0f, 1.0f - C.st * C.st)) : 0.0f;
+  return C;
+}
+
+// Whether the ball (x, y, z, radius rho) may reach the cone: the distance of
+// its centre from the cone's surface, |c x a| ct - (c.a) st with c the centre
+// relative to the apex, is at most rho (it is negative inside; a centre
+// nearer to the apex than to the surface is further away than that).  The
+// margin covers the rounding of c and of the products (a few 1e-7 |c|).
+__device__ inline bool ray_cone_meets(const RayCone& C, float x, float y, float z, float rho) {
+  if (C.st > 1.0f) return true;
+  const float cx = x - C.ox, cy = y - C.oy, cz = z - C.oz;
+  const float par = cx * C.ax + cy * C.ay + cz * C.az;
+  const float ux = cy * C.az - cz * C.ay, uy = cz * C.ax - cx * C.az, uz = cx * C.ay - cy * C.ax;
+  const float perp = fsqrt(ux * ux + uy * uy + uz * uz);
+  const float far = fabsf(cx) + fabsf(cy) + fabsf(cz) + fabsf(C.ox) + fabsf(C.oy) + fabsf(C.oz);
+  return !(perp * C.ct - par * C.st > rho * (1.0f + 1e-5f) + 4e-6f * far + 1e-7f);
+}
+
+// Pixels of a wave as points u = (d.b1, d.b2) / (d.a) of the plane at unit
+// distance along the axis a of its cone, b1 and b2 completing a to a frame.
+// A ball whose centre projects to w at depth z = c.a meets the ray of u only
+// if |c x d| <= rho, and |c x d|^2 >= z^2 |w - u|^2 / (1 + |u|^2), so the
+// nearest of the 64 points decides whether any ray of the wave can meet it:
+// balls that fall between the pixel centres are dropped, 64 cells at a time.
+struct RayGrid {
+  float b1x, b1y, b1z, b2x, b2y, b2z, k;   // k = 1 + largest |u|^2
+};
+
+__device__ inline RayGrid ray_grid(const RayD& R, const RayCone& C, bool use, float2& u) {
+  RayGrid G;
+  onb(C.ax, C.ay, C.az, G.b1x, G.b1y, G.b1z, G.b2x, G.b2y, G.b2z);
+  const float par = R.fx * C.ax + R.fy * C.ay + R.fz * C.az;
+  const float inv = use && par > 0.0f ? 1.0f / par : 0.0f;
+  // (a pixel without a ray is put out of reach)
+  u.x = use ? (R.fx * G.b1x + R.fy * G.b1y + R.fz * G.b1z) * inv : 1e18f;
+  u.y = use ? (R.fx * G.b2x + R.fy * G.b2y + R.fz * G.b2z) * inv : 1e18f;
+  const float m = -wave_min_f(use ? -(u.x * u.x + u.y * u.y) : 0.0f);
+  G.k = (1.0f + m) * (1.0f + 1e-5f);
+  return G;
+}
+
+// Whether the ball may meet one of the rays u[0..63] (pairs of points).
+__device__ inline bool ray_grid_meets(const RayCone& C, const RayGrid& G, const float4* u2, float x, float y, float z,
+                                      float rho) {
+  if (C.st > 1.0f) return true;
+  const float cx = x - C.ox, cy = y - C.oy, cz = z - C.oz;
+  const float far = fabsf(cx) + fabsf(cy) + fabsf(cz) + fabsf(C.ox) + fabsf(C.oy) + fabsf(C.oz);
+  const float r = rho * (1.0f + 1e-5f) + 4e-6f * far + 1e-7f;
+  const float depth = cx * C.ax + cy * C.ay + cz * C.az;
+  if (!(depth > 2.0f * r)) return true;   // around or behind the camera
+  const float inv = 1.0f / depth;
+  const float wx = (cx * G.b1x + cy * G.b1y + cz * G.b1z) * inv, wy = (cx * G.b2x + cy * G.b2y + cz * G.b2z) * inv;
+  float best = INFINITY;
+#pragma unroll 4
+  for (int j = 0; j < 32; ++j) {
+    const float4 p = u2[j];
+    const float ex = wx - p.x, ey = wy - p.y, gx = wx - p.z, gy = wy - p.w;
+    best = fminf(best, fminf(ex * ex + ey * ey, gx * gx + gy * gy));
+  }
+  return !(best * depth * depth > r * r * G.k);
+}
+
 // COUNT: the work counters of the composite are added to counters[0..5]
 // (RASTER_COUNTERS): pixel-cell tests, sphere hits, contributions, and the
 // (wave, cell) steps that tested, that computed a piece, that shaded.
+struct RasterCounts {
+  unsigned long long test = 0, hit = 0, contrib = 0, step = 0, step_hit = 0, step_shade = 0;
+  __device__ void add(unsigned long long* __restrict__ c) const {
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&c[0], test);
+      atomicAdd(&c[1], hit);
+      atomicAdd(&c[2], contrib);
+      atomicAdd(&c[3], step);
+      atomicAdd(&c[4], step_hit);
+      atomicAdd(&c[5], step_shade);
+    }
+  }
+};
+
+// Which tiles of a launch go to k_raster_split: those whose list is longer
+// than plan[PLAN_LEN], listed (longest first, by classes of 1/8 of a power of
+// two) in plan[PLAN_LIST ...], plan[PLAN_COUNT] of them; plan[PLAN_NEXT] is the
+// queue of k_raster_split, zeroed here.
+//
+// With t the length, S(t) the entries of all lists up to t and SLOTS the tiles
+// that the chip holds at once, k_raster takes about max(CHAIN t, S(t) / SLOTS):
+// its longest list, walked by one wave per quadrant, or its share of the
+// whole; k_raster_split takes about SPLIT_COST (S - S(t)) / SLOTS for the rest,
+// its waves being less full.  The t of the least sum is taken.  (CHAIN and
+// SPLIT_COST from whole launches through either kernel: 10.5 ms or 1.0 ms for
+// 256x256 at 1,048,576 cells, 256 tiles; 2.25 or 2.06 ms, 1.83 ms as planned,
+// for 1280x720 at 262,144; 29.7 or 52.8 ms for 8 views of 1600x1066 at
+// 1,048,576, where the plan keeps k_raster.)
+constexpr int PLAN_LEN = 0, PLAN_COUNT = 1, PLAN_NEXT = 2, PLAN_LIST = 4;
+constexpr int PLAN_THREADS = 1024, PLAN_CLASSES = 256;
+constexpr float SLOTS = 256.0f * 7.0f, CHAIN = 1.5f, SPLIT_COST = 1.5f;
+
+// Length class: lengths below 16 by themselves, then eight classes per power
+// of two; class_max is the largest length of a class.
+__device__ inline int len_class(uint32_t len) {
+  if (len < 16) return (int)len;
+  const int e = 31 - __clz(len);
+  return 16 + 8 * (e - 4) + (int)((len >> (e - 3)) & 7u);
+}
+__device__ inline uint32_t class_max(int c) {
+  if (c < 16) return (uint32_t)c;
+  const int e = (c - 16) / 8 + 4, f = (c - 16) % 8;
+  return (uint32_t)((((unsigned long long)(9 + f)) << (e - 3)) - 1);
+}
+
+__global__ void __launch_bounds__(PLAN_THREADS) k_split_plan(const uint32_t* __restrict__ tile_off, int64_t tile_first,
+                                                             int64_t count, uint32_t* __restrict__ plan) {
+  constexpr int REP = 8;   // copies of the histogram (fewer lanes meet on one word)
+  __shared__ uint32_t s_n[REP][PLAN_CLASSES], s_sum[REP][PLAN_CLASSES];
+  __shared__ uint32_t s_pos[PLAN_CLASSES];
+  __shared__ uint32_t s_part[4][2];
+  __shared__ float s_cost[4];
+  __shared__ int s_cls[4], s_best;
+  __shared__ uint32_t s_count;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, rep = t & (REP - 1);
+  for (int k = t; k < REP * PLAN_CLASSES; k += PLAN_THREADS) {
+    (&s_n[0][0])[k] = 0;
+    (&s_sum[0][0])[k] = 0;
+  }
+  __syncthreads();
+  // (eight loads in flight per thread)
+  auto each = [&](auto&& fn) {
+    for (int64_t i0 = 0; i0 < count; i0 += 8 * PLAN_THREADS) {
+      uint32_t len[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int64_t i = i0 + k * PLAN_THREADS + t;
+        len[k] = i < count ? tile_off[tile_first + i + 1] - tile_off[tile_first + i] : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (len[k]) fn((uint32_t)(i0 + k * PLAN_THREADS + t), len[k]);
+    }
+  };
+  each([&](uint32_t, uint32_t len) {
+    const int c = len_class(len);
+    atomicAdd(&s_n[rep][c], 1u);
+    atomicAdd(&s_sum[rep][c], len);
+  });
+  __syncthreads();
+  // a thread per class: prefix sums of the lists and their entries, and the
+  // least cost with its class
+  uint32_t n = 0, len = 0, n_in = 0, len_in = 0;
+  if (t < PLAN_CLASSES) {
+    for (int r = 0; r < REP; ++r) {
+      n += s_n[r][t];
+      len += s_sum[r][t];
+    }
+    n_in = n;
+    len_in = len;
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t a = __shfl_up(n_in, d, 64), b = __shfl_up(len_in, d, 64);
+      if (lane >= d) {
+        n_in += a;
+        len_in += b;
+      }
+    }
+    if (lane == 63) {
+      s_part[wave][0] = n_in;
+      s_part[wave][1] = len_in;
+    }
+  }
+  __syncthreads();
+  const uint32_t n_all = s_part[0][0] + s_part[1][0] + s_part[2][0] + s_part[3][0];
+  const uint32_t len_all = s_part[0][1] + s_part[1][1] + s_part[2][1] + s_part[3][1];
+  if (t < PLAN_CLASSES) {
+    for (int w = 0; w < wave; ++w) {
+      n_in += s_part[w][0];
+      len_in += s_part[w][1];
+    }
+    // (class 0, no lists of any length: everything is split)
+    float cost = n || t == 0 ? fmaxf(CHAIN * (float)class_max(t), (float)len_in / SLOTS) +
+                                   SPLIT_COST * (float)(len_all - len_in) / SLOTS
+                             : INFINITY;
+    int cls = t;
+    for (int o = 32; o > 0; o >>= 1) {
+      const float c2 = __shfl_xor(cost, o, 64);
+      const int k2 = __shfl_xor(cls, o, 64);
+      if (c2 < cost || (c2 == cost && k2 > cls)) {
+        cost = c2;
+        cls = k2;
+      }
+    }
+    if (lane == 0) {
+      s_cost[wave] = cost;
+      s_cls[wave] = cls;
+    }
+    s_pos[t] = n_all - n_in;   // lists of the longer classes come first
+  }
+  __syncthreads();
+  if (t == 0) {
+    int w = 0;
+    for (int k = 1; k < 4; ++k)
+      if (s_cost[k] <= s_cost[w]) w = k;
+    s_best = s_cls[w];
+    s_count = 0;
+    plan[PLAN_LEN] = class_max(s_cls[w]);
+    plan[PLAN_NEXT] = 0;
+  }
+  __syncthreads();
+  if (t == s_best) {
+    s_count = n_all - n_in;
+    plan[PLAN_COUNT] = n_all - n_in;
+  }
+  __syncthreads();
+  const int bc = s_best;
+  if (s_count == 0) return;
+  each([&](uint32_t i, uint32_t len) {
+    const int c = len_class(len);
+    if (c > bc) plan[PLAN_LIST + atomicAdd(&s_pos[c], 1u)] = i;
+  });
+}
+
 // Seven waves per SIMD (at most 72 VGPRs) are asked for explicitly: the
-// compiler's own choice lands a few registers above, at six.
+// compiler's own choice lands a few registers above, at six.  Tiles whose
+// list is longer than plan[PLAN_LEN] are left to k_raster_split.
 template <bool STORE, bool COUNT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
 k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigned long long* __restrict__ list,
          const uint32_t* __restrict__ tile_off, float t_min, float* __restrict__ rgba_all, int4* __restrict__ rec_ri,
          float4* __restrict__ rec_rf, float* __restrict__ rec_rt, int32_t* __restrict__ rec_head,
          unsigned long long* __restrict__ rec_counter, int4* __restrict__ rec_seg, int2* __restrict__ rec_wtail,
-         int64_t tile_first, int64_t wtail_base, int64_t rec_cap, int64_t seg_cap,
+         int64_t wtail_base, int64_t rec_cap, int64_t seg_cap,
+         int64_t tile_first, const uint32_t* __restrict__ plan,
          unsigned long long* __restrict__ counters) {
   // the tile's sorted cells are staged RB at a time: list entry and the cell
   // record fields every lane needs, loaded by the whole workgroup at once
@@ -438,6 +771,8 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
   __shared__ int s_row[RB];
   __shared__ int s_nr[RB];
   __shared__ int s_more[4];
+  __shared__ RayCone s_cone[4];   // per wave
+  const RecOut O{rec_ri, rec_rf, rec_rt, rec_counter, rec_seg, rec_cap, seg_cap};
 
   // one workgroup per work item (a tile of one of the launch's views); the
   // hardware dispatcher hands the next item to whichever CU frees up, so the
@@ -445,18 +780,12 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
   // the CUs.  (A persistent loop over items held twice the registers and
   // halved the occupancy.)
   const int64_t item = blockIdx.x;
-  // tile of the view group; its view: the last one whose tiles start at or before it
   const int64_t gtile = tile_first + item;
-  int lo = 0, hi = nview - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (views[mid].tile_base <= (long long)gtile) lo = mid; else hi = mid - 1;
-  }
-  const ViewDev& vd = views[lo];
-  const int view = vd.view_id;
+  const uint32_t e0 = tile_off[gtile], e1 = tile_off[gtile + 1];
+  if (e1 - e0 > plan[PLAN_LEN]) return;
+  const ViewDev& vd = tile_view(views, nview, gtile);
   const ViewArgs& v = vd.v;
-  const int64_t pix_base = vd.pix_base;
-  float* rgba = rgba_all + 4 * pix_base;
+  float* rgba = rgba_all + 4 * vd.pix_base;
   int px, py;
   tile_pixel(v.tiles_x, px, py, (int)(gtile - vd.tile_base));
   const bool inside = px < v.cam.width && py < v.cam.height;
@@ -467,11 +796,12 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int pix = py * v.cam.width + px;
-  const uint32_t e0 = tile_off[gtile], e1 = tile_off[gtile + 1];
-  long long rblk = 0, sblk = 0;   // the wave's current record / segment block
-  long long cblk = -1;            // first slot (header) of the wave's current segment block
-  int rleft = 0, sleft = 0;
-  unsigned long long n_test = 0, n_hit = 0, n_contrib = 0, n_step = 0, n_step_hit = 0, n_step_shade = 0;
+  WaveSlots W;
+  RasterCounts N;
+  {
+    const RayCone cone = ray_cone(R, live);
+    if (lane == 0) s_cone[wave] = cone;
+  }
   for (uint32_t b0 = e0; b0 < e1; b0 += RB) {
     {
       const uint32_t e = b0 + threadIdx.x;
@@ -486,84 +816,65 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
       }
     }
     __syncthreads();
+    // the cells whose ball can meet a ray of the wave's quadrant, found 64 at
+    // a time, one per lane; only those are tested pixel by pixel
     const int nb = (int)min((uint32_t)RB, e1 - b0);
-    for (int q = 0; q < nb; ++q) {
-      if (!__any(live)) break;
-      const int ci = __builtin_amdgcn_readfirstlane(s_ci[q]);
-      const float4 g = s_geo[q];
-      const float rho = s_rho[q];
-      const Local L = make_local(R, g.x, g.y, g.z);
-      const bool hit = live && (rho >= 0.0f) && (L.qq < (double)rho * (double)rho);
-      if constexpr (COUNT) {
-        n_test += (unsigned long long)__popcll(__ballot(live));
-        n_hit += (unsigned long long)__popcll(__ballot(hit));
-        ++n_step;
+#pragma unroll 1
+    for (int k0 = 0; k0 < nb; k0 += 64) {
+      uint64_t todo;
+      {
+        const RayCone cone = s_cone[wave];
+        const int q = k0 + lane;
+        const float4 g = s_geo[q];
+        const float rho = s_rho[q];
+        todo = __ballot(q < nb && rho >= 0.0f && ray_cone_meets(cone, g.x, g.y, g.z, rho));
       }
-      if (!__any(hit)) continue;
-      if constexpr (COUNT) ++n_step_hit;
-      const float* tx = S.tex + (int64_t)ci * (KD * TEXW);
-      Piece P;
-      P.alpha = 0.0f;
-      float r = 0.0f, gg = 0.0f, b = 0.0f;
-      if (hit) {
-        P = piece_geometry<true>(R, L, g.w, S.plane + __builtin_amdgcn_readfirstlane(s_row[q]),
-                           __builtin_amdgcn_readfirstlane(s_nr[q]), s_nrm[q], tx, S.tau);
-        if (P.alpha > 0.0f) radiance<true>(tx, S.rgb + 3 * (int64_t)ci, P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
-      }
-      const bool contrib = hit && P.alpha > 0.0f;
-      if constexpr (COUNT) {
-        const uint64_t mc = __ballot(contrib);
-        n_contrib += (unsigned long long)__popcll(mc);
-        n_step_shade += mc ? 1ull : 0ull;
-      }
-      if constexpr (STORE) {
-        const uint64_t m = __ballot(contrib);
-        if (m) {
-          // slots come from the wave's own blocks; a new block is reserved
-          // with one global atomic when the current one cannot take the append
-          const int cnt = __popcll(m);
-          if (cnt > rleft) {
-            unsigned long long bk = 0;
-            if (lane == 0) bk = atomicAdd(&rec_counter[0], (unsigned long long)RBLK);
-            rblk = (long long)bcast64(bk);
-            rleft = RBLK;
-          }
-          if (sleft == 0) {
-            unsigned long long bk = 0;
-            if (lane == 0) bk = atomicAdd(&rec_counter[1], (unsigned long long)SBLK);
-            const long long nb = (long long)bcast64(bk);
-            // the block's header links it to the wave's previous block
-            if (lane == 0 && nb < seg_cap) rec_seg[nb] = make_int4(-1, (int)cblk, 0, 0);
-            cblk = nb;
-            sblk = nb + 1;
-            sleft = SBLK - 1;
-          }
-          const long long base = rblk, sg = sblk;
-          rblk += cnt;
-          rleft -= cnt;
-          sblk += 1;
-          sleft -= 1;
-          if (lane == 0 && sg < seg_cap && base + cnt <= rec_cap)
-            rec_seg[sg] = make_int4(ci, (int)base, (int)(uint32_t)m, (int)(uint32_t)(m >> 32));
-          if (contrib) {
-            const long long slot = base + __popcll(m & lt);
-            if (slot < rec_cap) {
-              rec_ri[slot] = make_int4(ci, pix, head, pack_view_bind(view, P.bind0, P.bind1));
-              rec_rf[slot] = make_float4(P.alpha, r, gg, b);
-              rec_rt[slot] = T;
-              head = (int)slot;
-            }
-          }
+      for (; todo; todo &= todo - 1) {
+        if (!__any(live)) break;
+        const int q = k0 + __ffsll((long long)todo) - 1;
+        const int ci = __builtin_amdgcn_readfirstlane(s_ci[q]);
+        const float4 g = s_geo[q];
+        const float rho = s_rho[q];
+        const Local L = make_local(R, g.x, g.y, g.z);
+        const bool hit = live && (L.qq < (double)rho * (double)rho);
+        if constexpr (COUNT) {
+          N.test += (unsigned long long)__popcll(__ballot(live));
+          N.hit += (unsigned long long)__popcll(__ballot(hit));
+          ++N.step;
         }
+        if (!__any(hit)) continue;
+        if constexpr (COUNT) ++N.step_hit;
+        const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
+        Piece P;
+        P.alpha = 0.0f;
+        float r = 0.0f, gg = 0.0f, b = 0.0f;
+        if (hit) {
+          P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(s_row[q])),
+                             __builtin_amdgcn_readfirstlane(s_nr[q]), s_nrm[q], tx, S.tau);
+          if (P.alpha > 0.0f)
+            radiance_wave(tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
+        }
+        const bool contrib = hit && P.alpha > 0.0f;
+        if constexpr (COUNT) {
+          const uint64_t mc = __ballot(contrib);
+          N.contrib += (unsigned long long)__popcll(mc);
+          N.step_shade += mc ? 1ull : 0ull;
+        }
+        if constexpr (STORE) {
+          const uint64_t m = __ballot(contrib);
+          if (m)
+            append_records(O, W, m, lane, lt, ci, pix, pack_view_bind(vd.view_id, P.bind0, P.bind1), P.alpha, r, gg, b,
+                           T, head);
+        }
+        if (contrib) {
+          const float wgt = T * P.alpha;
+          cr += wgt * r;
+          cg += wgt * gg;
+          cb += wgt * b;
+          T *= (1.0f - P.alpha);
+        }
+        live = live && (T >= t_min);
       }
-      if (contrib) {
-        const float wgt = T * P.alpha;
-        cr += wgt * r;
-        cg += wgt * gg;
-        cb += wgt * b;
-        T *= (1.0f - P.alpha);
-      }
-      live = live && (T >= t_min);
     }
     const bool wl = __any(live);
     if (lane == 0) s_more[wave] = wl ? 1 : 0;
@@ -578,24 +889,278 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
     o[1] = cg;
     o[2] = cb;
     o[3] = 1.0f - T;
-    if constexpr (STORE) rec_head[pix_base + pix] = head;
+    if constexpr (STORE) rec_head[vd.pix_base + pix] = head;
   }
-  if constexpr (STORE) {
-    // unused slots of the last segment block are marked empty (mask 0)
-    for (int j = lane; j < sleft; j += 64)
-      if (sblk + j < seg_cap) rec_seg[sblk + j] = make_int4(0, 0, 0, 0);
-    if (lane == 0) rec_wtail[(wtail_base + item) * 4 + wave] = make_int2((int)cblk, SBLK - sleft);
+  if constexpr (STORE) close_segments(O, W, lane, rec_wtail + (wtail_base + item) * 4 + wave);
+  if constexpr (COUNT) N.add(counters);
+}
+
+// Waits until *p >= v (32-bit counters in LDS written by another wave of the
+// workgroup); returns false if *stop became 0 first.
+__device__ inline bool lds_wait(const int* p, int v, const unsigned long long* stop) {
+  while (__hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < v) {
+    if (stop && __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0ull) return false;
+    __builtin_amdgcn_s_sleep(1);
   }
-  if constexpr (COUNT) {
-    if (lane == 0) {
-      atomicAdd(&counters[0], n_test);
-      atomicAdd(&counters[1], n_hit);
-      atomicAdd(&counters[2], n_contrib);
-      atomicAdd(&counters[3], n_step);
-      atomicAdd(&counters[4], n_step_hit);
-      atomicAdd(&counters[5], n_step_shade);
+  return true;
+}
+
+// The same composite for the tiles with long lists: a workgroup of NW waves
+// per 8x8 quadrant of a tile.  Opacity and colour of a (pixel, cell) pair do
+// not depend on the cells in front of it, so NW - 1 waves evaluate the cells
+// of the list, each taking the next one over the quadrant's 64 pixels, and
+// one wave composites their results in list order: the arithmetic of a
+// pixel is that of k_raster, operation for operation.  The list is first
+// reduced, a step of 64 NW entries at a time and one cell per lane, to the
+// cells whose ball can meet one of the quadrant's rays; those are queued.
+//
+// A tile's list is a serial chain for its four waves in k_raster: with few
+// tiles, or a few long ones among many, the chip idles behind those chains.
+//
+// Results pass through a ring of RING slots in LDS: a slot holds cell j of
+// the queue once s_flag of the slot reads base + j + 1, and is free for cell
+// j + RING once s_done > base + j (base: cells of the earlier steps).  The
+// evaluating waves take cells in order and the compositing wave waits for
+// them in order, so the first cell not yet composited is always being
+// evaluated in a slot of its own, and both sides finish; when no pixel is
+// left (s_live = 0) the evaluating waves stop waiting for slots.  The
+// workgroups take the quadrants of the plan's tiles from a queue, longest
+// lists first.
+constexpr int NW = 16;
+template <bool STORE, bool COUNT>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
+k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigned long long* __restrict__ list,
+               const uint32_t* __restrict__ tile_off, float t_min, float* __restrict__ rgba_all,
+               int4* __restrict__ rec_ri, float4* __restrict__ rec_rf, float* __restrict__ rec_rt,
+               int32_t* __restrict__ rec_head, unsigned long long* __restrict__ rec_counter,
+               int4* __restrict__ rec_seg, int2* __restrict__ rec_wtail, int64_t wtail_base, int64_t rec_cap,
+               int64_t seg_cap, int64_t tile_first, uint32_t* plan, unsigned long long* __restrict__ counters) {
+  constexpr int CH = 64 * NW;      // list entries culled at a time
+  constexpr int RING = 2 * NW;
+  __shared__ int q_ci[CH];
+  __shared__ float4 q_geo[CH];
+  __shared__ float4 q_nrm[CH];
+  __shared__ float q_rho[CH];
+  __shared__ int q_row[CH];
+  __shared__ int q_nr[CH];
+  __shared__ float4 s_res[RING][64];               // (alpha, colour) per pixel
+  __shared__ int s_bind[STORE ? RING : 1][64];
+  __shared__ unsigned long long s_mask[RING];      // the pixels the cell contributes to
+  __shared__ int s_cell[RING];
+  __shared__ int s_flag[RING];
+  __shared__ int s_done;                           // cells composited
+  __shared__ int s_next;                           // next cell of the queue to evaluate
+  __shared__ unsigned long long s_live;            // pixels not yet opaque
+  __shared__ int s_cnt[NW];
+  __shared__ float4 s_u2[32];                      // the pixels as points (RayGrid)
+  __shared__ RayCone s_cone;
+  __shared__ RayGrid s_grid;
+  __shared__ uint32_t s_item;
+  static_assert(RING <= 64, "flags cleared by one wave");
+
+  const uint32_t n_items = 4 * plan[PLAN_COUNT];
+  RasterCounts N;
+  for (;;) {
+    if (threadIdx.x == 0) s_item = atomicAdd(&plan[PLAN_NEXT], 1u);
+    __syncthreads();
+    const uint32_t qi = __builtin_amdgcn_readfirstlane(s_item);
+    if (qi >= n_items) break;
+    const int64_t item = plan[PLAN_LIST + qi / 4];
+    const int quad = qi & 3;
+    const int64_t gtile = tile_first + item;
+    const ViewDev& vd = tile_view(views, nview, gtile);
+    const ViewArgs& v = vd.v;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ltile = (int)(gtile - vd.tile_base);
+    const int px = (ltile % v.tiles_x) * TILE + (quad & 1) * 8 + (lane & 7);
+    const int py = (ltile / v.tiles_x) * TILE + (quad >> 1) * 8 + (lane >> 3);
+    const bool inside = px < v.cam.width && py < v.cam.height;
+    const RayD R = make_ray(v.cam, px + 0.5, py + 0.5);
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t e0 = tile_off[gtile], e1 = tile_off[gtile + 1];
+    if (wave == 0) {
+      const bool use = inside && R.valid;
+      const RayCone cone = ray_cone(R, use);
+      float2 u;
+      const RayGrid grid = ray_grid(R, cone, use, u);
+      ((float2*)s_u2)[lane] = u;
+      const uint64_t l = __ballot(use);
+      if (lane == 0) {
+        s_cone = cone;
+        s_grid = grid;
+        s_live = l;
+        s_done = 0;
+        s_next = 0;
+      }
+      if (lane < RING) s_flag[lane] = 0;
     }
+    __syncthreads();
+
+    // Queues the cells of the list entries [b0, b0 + CH) that can meet a ray
+    // of the quadrant; returns their number (all waves take part).
+    auto cull = [&](uint32_t b0) -> int {
+      const uint32_t e = b0 + threadIdx.x;
+      int c = -1;
+      float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      float rho = -1.0f;
+      if (e < e1) {
+        c = (int)(uint32_t)list[e];
+        g = S.geo[c];
+        rho = S.cull[c];
+      }
+      const RayCone cone = s_cone;
+      bool keep = rho >= 0.0f && ray_cone_meets(cone, g.x, g.y, g.z, rho);
+      if (keep) keep = ray_grid_meets(cone, s_grid, s_u2, g.x, g.y, g.z, rho);
+      const uint64_t km = __ballot(keep);
+      if (lane == 0) s_cnt[wave] = __popcll(km);
+      float4 nr4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      int row = 0, nrast = 0;
+      if (keep) {
+        nr4 = S.nrm[c];
+        row = S.row[c];
+        nrast = S.nrast[c];
+      }
+      __syncthreads();
+      int at = __popcll(km & lt), total = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const int n = s_cnt[w];
+        at += w < wave ? n : 0;
+        total += n;
+      }
+      if (keep) {
+        q_ci[at] = c;
+        q_geo[at] = g;
+        q_nrm[at] = nr4;
+        q_rho[at] = rho;
+        q_row[at] = row;
+        q_nr[at] = nrast;
+      }
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(total);
+    };
+
+    int base = 0;   // cells queued by the earlier steps
+    if (wave == 0) {
+      // --- the compositing wave
+      const RecOut O{rec_ri, rec_rf, rec_rt, rec_counter, rec_seg, rec_cap, seg_cap};
+      bool live = inside && R.valid;
+      float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+      int head = -1;
+      const int pix = py * v.cam.width + px;
+      WaveSlots W;
+      uint64_t lm = __ballot(live);
+      for (uint32_t b0 = e0; b0 < e1; b0 += CH) {
+        const int nq = cull(b0);
+        for (int j = 0; j < nq && lm; ++j) {
+          const int slot = (base + j) % RING;
+          lds_wait(&s_flag[slot], base + j + 1, nullptr);
+          const uint64_t m = bcast64(s_mask[slot]) & lm;
+          if (m) {
+            const bool contrib = (m >> lane) & 1ull;
+            const float4 c = s_res[slot][lane];
+            if constexpr (COUNT) {
+              N.contrib += (unsigned long long)__popcll(m);
+              ++N.step_shade;
+            }
+            if constexpr (STORE)
+              append_records(O, W, m, lane, lt, __builtin_amdgcn_readfirstlane(s_cell[slot]), pix, s_bind[slot][lane],
+                             c.x, c.y, c.z, c.w, T, head);
+            if (contrib) {
+              const float wgt = T * c.x;
+              cr += wgt * c.y;
+              cg += wgt * c.z;
+              cb += wgt * c.w;
+              T *= (1.0f - c.x);
+            }
+            live = live && (T >= t_min);
+            lm = __ballot(live);
+          }
+          if (lane == 0) {
+            __hip_atomic_store(&s_live, (unsigned long long)lm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&s_done, base + j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
+        base += nq;
+        __syncthreads();
+        if (lane == 0) s_next = 0;
+        __builtin_amdgcn_wave_barrier();
+        if (!lm) break;
+      }
+      if (inside) {
+        float* o = rgba_all + 4 * (vd.pix_base + (int64_t)py * v.cam.width + px);
+        o[0] = cr;
+        o[1] = cg;
+        o[2] = cb;
+        o[3] = 1.0f - T;
+        if constexpr (STORE) rec_head[vd.pix_base + pix] = head;
+      }
+      if constexpr (STORE) close_segments(O, W, lane, rec_wtail + (wtail_base + item) * 4 + quad);
+    } else {
+      // --- the evaluating waves
+      for (uint32_t b0 = e0; b0 < e1; b0 += CH) {
+        const int nq = cull(b0);
+        for (;;) {
+          int j = 0;
+          if (lane == 0) j = atomicAdd(&s_next, 1);
+          __builtin_amdgcn_wave_barrier();
+          j = __builtin_amdgcn_readfirstlane(j);
+          if (j >= nq) break;
+          const int ci = __builtin_amdgcn_readfirstlane(q_ci[j]);
+          const float4 g = q_geo[j];
+          const float rho = q_rho[j];
+          // (pixels only leave the set, so an older value costs work, not results)
+          const uint64_t lm = bcast64(
+              __hip_atomic_load(&s_live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+          if (!lm) break;
+          const Local L = make_local(R, g.x, g.y, g.z);
+          const bool hit = ((lm >> lane) & 1ull) && (L.qq < (double)rho * (double)rho);
+          if constexpr (COUNT) {
+            const uint64_t hm = __ballot(hit);
+            N.test += (unsigned long long)__popcll(lm);
+            N.hit += (unsigned long long)__popcll(hm);
+            ++N.step;
+            N.step_hit += hm ? 1ull : 0ull;
+          }
+          Piece P;
+          P.alpha = 0.0f;
+          float r = 0.0f, gg = 0.0f, b = 0.0f;
+          if (hit) {
+            const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
+            P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(q_row[j])),
+                                     __builtin_amdgcn_readfirstlane(q_nr[j]), q_nrm[j], tx, S.tau);
+            if (P.alpha > 0.0f)
+              radiance_wave(tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
+          }
+          const bool contrib = hit && P.alpha > 0.0f;
+          const uint64_t m = __ballot(contrib);
+          const int slot = (base + j) % RING;
+          if (!lds_wait(&s_done, base + j - RING + 1, &s_live)) break;
+          if (contrib) {
+            s_res[slot][lane] = make_float4(P.alpha, r, gg, b);
+            if constexpr (STORE) s_bind[slot][lane] = pack_view_bind(vd.view_id, P.bind0, P.bind1);
+          }
+          if (lane == 0) {
+            s_mask[slot] = m;
+            s_cell[slot] = ci;
+          }
+          // (the wave's LDS writes complete in order before the flag is set)
+          if (lane == 0)
+            __hip_atomic_store(&s_flag[slot], base + j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          // the wave stays together across the loop's end: without this the
+          // lanes other than 0 are sent past the next iteration's lane-0
+          // branch before lane 0 has taken its next cell
+          __builtin_amdgcn_wave_barrier();
+        }
+        base += nq;
+        __syncthreads();
+        if (!__hip_atomic_load(&s_live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+      }
+    }
+    __syncthreads();   // (the shared state is set up anew for the next quadrant)
   }
+  if constexpr (COUNT) N.add(counters);
 }
 
 // Total records listed by the segments (the block reservation leaves unused
@@ -736,7 +1301,7 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
         const int r0 = S.row[cell];
         P = piece_geometry<false>(R, L, g.w, S.plane + r0, S.nrast[cell], S.nrm[cell], tx, S.tau);
         if (P.alpha > 0.0f) {
-          radiance<false>(tx, S.rgb + 3 * (int64_t)cell, P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
+          radiance_lane(tx, S.rgb + 3 * (int64_t)cell, P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
           contrib = true;
         }
         if constexpr (COUNT) {
@@ -900,6 +1465,7 @@ int64_t raster_group_bytes(int64_t n, int nv, int64_t ntiles, int64_t np) {
   auto b = [](int64_t count, int64_t size) { return std::max<int64_t>(count, 1) * size; };
   const int64_t nvc = (int64_t)nv * n;
   return b(nv, sizeof(ViewDev)) + b(nvc + 1, 4) * 2 + b(nvc, 4) * 2 + b(ntiles + 1, 4) * 2 + b(ntiles, 4) +
+         b(PLAN_LIST + ntiles, 4) +
          b(1, 4) + scan_scratch_bytes(nvc + 1) + scan_scratch_bytes(ntiles + 1) + b(np, 4) + b(np, 8) * 2;
 }
 
@@ -912,11 +1478,11 @@ struct Group {
   int64_t ntiles = 0, tiles_before = 0, pix_before = 0;
   uint32_t np = 0;
   Buf<ViewDev> views;
-  Buf<uint32_t> cnt, key, off, tcnt, toff, fill, cone_list, cone_n, ptile;
+  Buf<uint32_t> cnt, key, off, tcnt, toff, fill, cone_list, cone_n, ptile, plan;
   Buf<unsigned long long> pval, sorted;
   explicit Group(hipStream_t s)
-      : views(s), cnt(s), key(s), off(s), tcnt(s), toff(s), fill(s), cone_list(s), cone_n(s), ptile(s), pval(s),
-        sorted(s) {}
+      : views(s), cnt(s), key(s), off(s), tcnt(s), toff(s), fill(s), cone_list(s), cone_n(s), ptile(s), plan(s),
+        pval(s), sorted(s) {}
 };
 
 // Cull and count (count_only: stops after the pair count), then emit,
@@ -947,6 +1513,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   PF_HIP_TRY(G.tcnt.alloc(ntiles + 1));
   PF_HIP_TRY(G.toff.alloc(ntiles + 1));
   PF_HIP_TRY(G.fill.alloc(ntiles));
+  PF_HIP_TRY(G.plan.alloc(PLAN_LIST + ntiles));
   PF_HIP_TRY(G.cone_list.alloc(nvc));
   PF_HIP_TRY(G.cone_n.alloc(1));
   PF_HIP_TRY(hipMemsetAsync(G.cone_n.p, 0, sizeof(uint32_t), s));
@@ -998,6 +1565,19 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   return PF_OK;
 }
 
+template <bool STORE, bool COUNT>
+void launch_raster(Scene& sc, Group& G, float t_min, float* rgba, hipStream_t s, const RecBuf& rb, int64_t first,
+                   int64_t count, int64_t wtail_base, unsigned long long* counters) {
+  k_split_plan<<<1, PLAN_THREADS, 0, s>>>(G.toff.p, first, count, G.plan.p);
+  // (one workgroup of sixteen waves per CU is resident)
+  k_raster_split<STORE, COUNT><<<(unsigned)std::min<int64_t>(4 * count, 256), 64 * NW, 0, s>>>(
+      G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
+      rb.seg, rb.wtail, wtail_base, rb.cap, rb.seg_cap, first, G.plan.p, counters);
+  k_raster<STORE, COUNT><<<(unsigned)count, 256, 0, s>>>(
+      G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
+      rb.seg, rb.wtail, wtail_base, rb.cap, rb.seg_cap, first, G.plan.p, counters);
+}
+
 // Composite of the group's tiles [first, first + count) (one launch, one
 // workgroup per tile); with records, the wave segment tails go to
 // rec->wtail from index wtail_base.
@@ -1005,25 +1585,12 @@ pf_status composite(Scene& sc, Group& G, float t_min, float* rgba, hipStream_t s
                     int64_t first, int64_t count, int64_t wtail_base, unsigned long long* counters) {
   if (count <= 0) return PF_OK;
   ProfScope ps(rec ? "k_raster_store" : "k_raster", s);
-  const unsigned grid = (unsigned)count;
   if (rec) {
-    const RecBuf& rb = *rec;
-    if (counters)
-      k_raster<true, true><<<grid, 256, 0, s>>>(G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba,
-                                                rb.ri, rb.rf, rb.rt, rb.head, rb.counter, rb.seg, rb.wtail, first,
-                                                wtail_base, rb.cap, rb.seg_cap, counters);
-    else
-      k_raster<true, false><<<grid, 256, 0, s>>>(G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba,
-                                                 rb.ri, rb.rf, rb.rt, rb.head, rb.counter, rb.seg, rb.wtail, first,
-                                                 wtail_base, rb.cap, rb.seg_cap, nullptr);
-  } else if (counters) {
-    k_raster<false, true><<<grid, 256, 0, s>>>(G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba,
-                                               nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, first, 0,
-                                               0, 0, counters);
+    if (counters) launch_raster<true, true>(sc, G, t_min, rgba, s, *rec, first, count, wtail_base, counters);
+    else launch_raster<true, false>(sc, G, t_min, rgba, s, *rec, first, count, wtail_base, nullptr);
   } else {
-    k_raster<false, false><<<grid, 256, 0, s>>>(G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba,
-                                                nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, first,
-                                                0, 0, 0, nullptr);
+    if (counters) launch_raster<false, true>(sc, G, t_min, rgba, s, RecBuf{}, first, count, 0, counters);
+    else launch_raster<false, false>(sc, G, t_min, rgba, s, RecBuf{}, first, count, 0, nullptr);
   }
   PF_HIP_TRY(hipGetLastError());
   return PF_OK;

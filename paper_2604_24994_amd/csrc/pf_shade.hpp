@@ -85,6 +85,23 @@ __device__ inline float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 // dozen instructions).
 __device__ inline float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
+// Read-only data whose address is the same in every lane of the wave, read
+// through the scalar cache: a pointer to the constant address space says so
+// whatever else the kernel writes (for an ordinary pointer the compiler has to
+// prove that no earlier store or atomic touches the data, and reads it into
+// vector registers, once per lane, when it cannot).  The data must not be
+// written while the kernel runs.
+typedef float vec4f __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) float* ufloat_p;
+typedef const __attribute__((address_space(4))) vec4f* uvec4_p;
+__device__ inline ufloat_p uniform_ptr(const float* p) { return (ufloat_p)p; }
+__device__ inline uvec4_p uniform_ptr(const float4* p) { return (uvec4_p)p; }
+__device__ inline float4 load4(const float4* p) { return *p; }
+__device__ inline float4 load4(uvec4_p p) {
+  const vec4f v = *p;
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 constexpr float LOG2E_F = 1.4426950408889634f;
 
 // exp(x - shift) as one fused multiply-add and the hardware exp2, with
@@ -174,7 +191,8 @@ __device__ inline float softmax2_sum(const float (&z)[N], float (&p)[N], float* 
 // Eq. svdisp / Eq. svrad).  The logits are shifted by tau*|u| and written as
 //   |u - s_k| - |u| = (|s_k|^2 - 2 u.s_k) / (|u - s_k| + |u|),
 // which keeps them accurate when u is far from the sites (grazing rays).
-__device__ inline void sv_weights(const float* __restrict__ tx, float ux, float uy, float tau, float* w) {
+template <typename FP>
+__device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w) {
   const float un = fsqrt(ux * ux + uy * uy);
   float mx = -INFINITY;
 #pragma unroll
@@ -238,9 +256,9 @@ struct Piece {
 // and, before the displacement weights, it tests whether the dense part is
 // empty for every displacement the sites allow (for the walk's per-lane loads
 // that test costs more than it saves).  Either way alpha is the same.
-template <bool WAVE_CELL>
-__device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, const float4* __restrict__ faces,
-                                       int nfaces, float4 nrm, const float* __restrict__ tx, float tau) {
+template <bool WAVE_CELL, typename VP, typename FP>
+__device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, VP faces, int nfaces, float4 nrm, FP tx,
+                                       float tau) {
   Piece P;
   P.alpha = 0.0f;
   P.ux = P.uy = 0.0f;
@@ -276,29 +294,29 @@ __device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, c
     bool more = nfaces >= 2;
     float4 c0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), c1 = c0;
     if (more) {
-      c0 = faces[0];
-      c1 = faces[1];
+      c0 = load4(faces);
+      c1 = load4(faces + 1);
     }
     while (more) {
       const float4 p0 = c0, p1 = c1;
       const int fn = f + 2;
       if (fn + 2 <= nfaces) {   // the next pair is loaded while this one is tested
-        const float4* fp = faces + __builtin_amdgcn_readfirstlane(fn);
-        c0 = fp[0];
-        c1 = fp[1];
+        const VP fp = faces + __builtin_amdgcn_readfirstlane(fn);
+        c0 = load4(fp);
+        c1 = load4(fp + 1);
       }
       clip(p0, f);
       clip(p1, f + 1);
       f = fn;
       more = f + 2 <= nfaces && __any(s0 < s1);
     }
-    if (f + 1 == nfaces) clip(faces[__builtin_amdgcn_readfirstlane(f)], f);
+    if (f + 1 == nfaces) clip(load4(faces + __builtin_amdgcn_readfirstlane(f)), f);
   } else {
     // (the next face is loaded while this one is tested)
-    float4 nxt = nfaces > 0 ? faces[0] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 nxt = nfaces > 0 ? load4(faces) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int f = 0; f < nfaces; ++f) {
       const float4 pl = nxt;
-      if (f + 1 < nfaces) nxt = faces[f + 1];
+      if (f + 1 < nfaces) nxt = load4(faces + f + 1);
       clip(pl, f);
     }
   }
@@ -372,16 +390,16 @@ __device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, c
 
 // Radiance at texture point u for direction d: base colour plus the
 // soft-Voronoi blend of the detail sites' Spherical-Voronoi colours.
-// WAVE_CELL = true (the rasteriser, one cell per wave, texture in scalar
-// registers): the lobes are exponentiated in base 2 without the max shift;
+// For the rasteriser (one cell per wave, texture in scalar registers): the
+// lobes are exponentiated in base 2 without the max shift;
 // if any site's sum leaves [2^-100, 2^100], the colour is evaluated again
 // with each site's logits shifted by their largest (as in softmax2_sum).
 // That rare pass runs over the sites in a loop that is not unrolled, so that
 // its texture reads are its own and the common pass holds no texture values
 // for it.
-template <bool WAVE_CELL>
-__device__ inline void radiance(const float* __restrict__ tx, const float* __restrict__ rgb, float ux, float uy,
-                                float fx, float fy, float fz, float tau, float& cr, float& cg, float& cb) {
+template <typename FP>
+__device__ inline void radiance_wave(FP tx, FP rgb, float ux, float uy, float fx, float fy, float fz, float tau,
+                                     float& cr, float& cg, float& cb) {
   float w[KD];
   sv_weights(tx, ux, uy, tau, w);
   const float gx = fx * LOG2E_F, gy = fy * LOG2E_F, gz = fz * LOG2E_F;
@@ -391,7 +409,7 @@ __device__ inline void radiance(const float* __restrict__ tx, const float* __res
   bool in_range = true;
 #pragma unroll
   for (int k = 0; k < KD; ++k) {
-    const float* t = tx + k * TEXW;
+    const FP t = tx + k * TEXW;
     float sum = 0.0f, sr = 0.0f, sg = 0.0f, sb = 0.0f;
 #pragma unroll
     for (int m = 0; m < MA; ++m) {
@@ -416,7 +434,7 @@ __device__ inline void radiance(const float* __restrict__ tx, const float* __res
       float wk = w[0];
 #pragma unroll
       for (int j = 1; j < KD; ++j) wk = (k == j) ? w[j] : wk;
-      const float* t = tx + k * TEXW;
+      const FP t = tx + k * TEXW;
       float mx = -INFINITY;
       for (int m = 0; m < MA; ++m) mx = fmaxf(mx, t[3 + 3 * m] * gx + t[4 + 3 * m] * gy + t[5 + 3 * m] * gz);
       float sum = 0.0f, sr = 0.0f, sg = 0.0f, sb = 0.0f;
@@ -437,13 +455,11 @@ __device__ inline void radiance(const float* __restrict__ tx, const float* __res
 }
 
 
-// WAVE_CELL = false (the walk: a cell per lane, the texture read per lane):
-// every softmax shifted by its largest logit, which keeps fewer values live
+// The same for the walk (a cell per lane, the texture read per lane): every softmax shifted by its largest logit, which keeps fewer values live
 // than the unshifted form with its rare shifted pass (the walk is held to 80
 // VGPRs).
-template <>
-__device__ inline void radiance<false>(const float* __restrict__ tx, const float* __restrict__ rgb, float ux, float uy,
-                                       float fx, float fy, float fz, float tau, float& cr, float& cg, float& cb) {
+__device__ inline void radiance_lane(const float* __restrict__ tx, const float* __restrict__ rgb, float ux, float uy,
+                                     float fx, float fy, float fz, float tau, float& cr, float& cg, float& cb) {
   float w[KD];
   sv_weights(tx, ux, uy, tau, w);
   cr = rgb[0];
