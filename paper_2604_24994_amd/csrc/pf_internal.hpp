@@ -48,12 +48,14 @@ struct Scene {
   float* cull = nullptr;           // radius of a ball at p bounding the
                                    // non-empty bounded cell; < 0: hidden
   int32_t* flags = nullptr;
-  int32_t* wit = nullptr;          // [n][8] per empty cell: sites that emptied it (next build's seeds)
+  int32_t* wit = nullptr;          // [n][8] per empty cell: planes that prove it empty, recent planes (pf_build.hip)
   // adjacency, CSR; per cell: raster faces, other neighbour faces, box faces
   int32_t* row = nullptr;          // [n+1]
   int32_t* nrast = nullptr;        // [n] faces that can cut the sphere
   int32_t* col = nullptr;          // [E] neighbour, or -1-f for box face f
   float4* plane = nullptr;         // [E] (m, h): (x - p_i).m <= h
+  int32_t* tri = nullptr;          // [2 E] per cell with F faces its 2 F - 4 vertices, as three face
+                                   // numbers of 8 bits (-1 first: not kept), for the next build
   int64_t n_faces = 0, n_hidden = 0, n_overflow = 0, n_big = 0, n_dropped = 0;
   double rec_per_pixel = 0.0;      // record-pool sizing hint for store mode (0: none yet)
   double seg_per_pixel = 0.0;      // segment-list sizing hint for store mode
