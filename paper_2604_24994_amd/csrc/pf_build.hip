@@ -722,6 +722,80 @@ __device__ void write_witness(const Shared<SPL, PM>& S, const Poly<SPL>& P, int 
   }
 }
 
+// A ball around the part of the cell that can contribute to an image: the
+// polytope where (x - p).n <= max(0, largest displacement), inside the sphere.
+// (The displaced face lies within the sites' displacements, so the dense side
+// does not reach past that plane; a ray along the face counts the side below
+// the undisplaced one.)  Its corners are the vertices on that side and the
+// points where the edges across the plane meet it.  The smaller of two balls
+// is taken: around p, of the sphere's radius at most, or around the middle of
+// the corners' box.  Cell-local centre and radius (no margin), radius -1 when
+// there are no corners.  All lanes take part.
+template <int SPL, int PM, typename EOT>
+__device__ float4 dense_ball(const Shared<SPL, PM>& S, const EOT* eo, const Poly<SPL>& P,
+                             const float* __restrict__ normal, float disp, float r) {
+  constexpr int NT = 64 * SPL;
+  const int lane = threadIdx.x;
+  const double ax = normal[0], ay = normal[1], az = normal[2];
+  const double inv = 1.0 / sqrt(ax * ax + ay * ay + az * az);
+  const double nx = ax * inv, ny = ay * inv, nz = az * inv;
+  const double top = fmax((double)disp, 0.0) * (1.0 + 1e-5) + 1e-7 * (double)r;
+  uint64_t above[SPL];
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) {
+    const int t = lane + 64 * s;
+    above[s] = __ballot(t < P.ntri && !(nx * P.x[s] + ny * P.y[s] + nz * P.z[s] <= top));
+  }
+  auto corners = [&](auto&& fn) {
+#pragma unroll
+    for (int s = 0; s < SPL; ++s) {
+      if (lane + 64 * s >= P.ntri) continue;
+      if (!((above[s] >> lane) & 1ull)) {
+        fn((float)P.x[s], (float)P.y[s], (float)P.z[s]);
+        continue;
+      }
+      int a, b, c;
+      unpack(P.id[s], a, b, c);
+      const int xs[3] = {a, b, c}, ys[3] = {b, c, a};
+      const double h0 = nx * P.x[s] + ny * P.y[s] + nz * P.z[s] - top;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int opp = (int)eo[ys[q] * PM + xs[q]] & (NT - 1);
+        uint64_t m = above[0];
+#pragma unroll
+        for (int t = 1; t < SPL; ++t) m = (opp >> 6) == t ? above[t] : m;
+        if ((m >> (opp & 63)) & 1ull) continue;
+        const double ox = S.tpos[opp][0], oy = S.tpos[opp][1], oz = S.tpos[opp][2];
+        const double h1 = nx * ox + ny * oy + nz * oz - top;   // <= 0 < h0
+        const double f = h0 * __builtin_amdgcn_rcp(h0 - h1);
+        fn((float)(P.x[s] + f * (ox - P.x[s])), (float)(P.y[s] + f * (oy - P.y[s])),
+           (float)(P.z[s] + f * (oz - P.z[s])));
+      }
+    }
+  };
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, far = -1.0f;
+  corners([&](float x, float y, float z) {
+    lo[0] = fminf(lo[0], x); hi[0] = fmaxf(hi[0], x);
+    lo[1] = fminf(lo[1], y); hi[1] = fmaxf(hi[1], y);
+    lo[2] = fminf(lo[2], z); hi[2] = fmaxf(hi[2], z);
+    far = fmaxf(far, x * x + y * y + z * z);
+  });
+  far = wave_max_dpp(far);
+  if (far < 0.0f) return make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = -wave_max_dpp(-lo[a]);
+    hi[a] = wave_max_dpp(hi[a]);
+  }
+  const float cx = 0.5f * (lo[0] + hi[0]), cy = 0.5f * (lo[1] + hi[1]), cz = 0.5f * (lo[2] + hi[2]);
+  float fc = 0.0f;
+  corners([&](float x, float y, float z) {
+    fc = fmaxf(fc, (x - cx) * (x - cx) + (y - cy) * (y - cy) + (z - cz) * (z - cz));
+  });
+  const float rc = sqrtf(wave_max_dpp(fc)), rp = fminf(r, sqrtf(far));
+  return rc < rp ? make_float4(cx, cy, cz, rc) : make_float4(0.0f, 0.0f, 0.0f, rp);
+}
+
 // MODE 0: all cells, sorted position k = blockIdx.x, faces at stride
 // FACE_CAP by original index, edge table in LDS.  MODE 1: the cells listed
 // in klist (sorted positions), faces at stride PM_BIG in slot blockIdx.x
@@ -743,7 +817,8 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
                                              const int32_t* __restrict__ wtri,
                                              const int32_t* __restrict__ wwit, const float4* __restrict__ wsp,
                                              const int32_t* __restrict__ wspos, int64_t wn,
-                                             int32_t* __restrict__ wit_out) {
+                                             int32_t* __restrict__ wit_out, const float* __restrict__ normal,
+                                             const float* __restrict__ tex, float4* __restrict__ ball) {
   constexpr bool LISTED = MODE >= 1, EO_HBM = MODE == 2;
   using EOT = typename std::conditional<(64 * SPL > 256), unsigned short, unsigned char>::type;
   static_assert(EO_HBM ? std::is_same<EOT, unsigned short>::value : true, "HBM edge table holds 16-bit slots");
@@ -1103,11 +1178,19 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
       counts[self] = 0;
       nrast[self] = 0;
       cull[self] = -1.0f;
+      ball[self] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
       const int why = status == OVER_V ? FLAG_OVER_VERTS : status == OVER_P ? FLAG_OVER_PLANES
                     : status == OVER_W ? FLAG_OVER_WORK : FLAG_OVER_STACK;
       flags[self] = is_empty(status) ? FLAG_EMPTY_POWER : (FLAG_OVERFLOW | why);
     }
     return;
+  }
+  // the largest displacement of the cell's face (loaded here, used at the end)
+  // (unbounded where a detail site is not finite: its weights are no convex combination then)
+  float disp = -INFINITY;
+  if (lane < KD) {
+    const float* t = tex + ((int64_t)self * KD + lane) * TEXW;
+    disp = fabsf(t[0]) + fabsf(t[1]) + fabsf(t[2]) < INFINITY ? t[2] : INFINITY;
   }
   for (int q = lane; q < PM; q += 64) S.used[q] = 0;
   __syncthreads();
@@ -1184,11 +1267,17 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
   viol = wave_max_d(viol);
   if (P.stale) update_bounds(S, P);
   const double R = sqrt(S.bd[BD_R2]);
+  const float dmax_f = wave_max_dpp(disp);
+  const float4 bl = dense_ball(S, eo, P, normal + 3 * (int64_t)self, dmax_f, (float)ri);
   if (lane == 0) {
     counts[self] = base;
     nrast[self] = nr;
     const bool hidden = viol > ri;
     cull[self] = hidden ? -1.0f : (float)fmin(ri, R * (1.0 + 1e-6));
+    // (the margin covers the rounding of the centre and of the pieces' float32 ends)
+    const double far = fabs(px) + fabs(py) + fabs(pz);
+    ball[self] = make_float4((float)(px + bl.x), (float)(py + bl.y), (float)(pz + bl.z),
+                             hidden || bl.w < 0.0f ? -1.0f : bl.w * (1.0f + 1e-4f) + (float)(1e-6 * far));
     flags[self] = 0;
   }
 }
@@ -1294,8 +1383,8 @@ __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, 
                                                  const int32_t* __restrict__ spos, int64_t n, float3 bmin, float3 bmax,
                                                  const int32_t* __restrict__ wit, int32_t* __restrict__ wit_out,
                                                  int32_t* __restrict__ counts, int32_t* __restrict__ nrast,
-                                                 float* __restrict__ cull, int32_t* __restrict__ flags,
-                                                 uint32_t* __restrict__ keep) {
+                                                 float* __restrict__ cull, float4* __restrict__ ball,
+                                                 int32_t* __restrict__ flags, uint32_t* __restrict__ keep) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int32_t self = sidx[k];
@@ -1358,6 +1447,7 @@ __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, 
     counts[self] = 0;
     nrast[self] = 0;
     cull[self] = -1.0f;
+    ball[self] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
     flags[self] = FLAG_EMPTY_POWER;
   }
 }
@@ -1440,7 +1530,7 @@ __device__ inline float softplus_f(float x) { return x > 20.0f ? x : log1pf(expf
 // logit is -inf) is never binned for the raster: it cannot contribute.
 __global__ void k_prep(const float* __restrict__ p, const float* __restrict__ r, const float* __restrict__ nrm,
                        const float* __restrict__ lam, float sigma_scale, int64_t n, float4* __restrict__ geo,
-                       float4* __restrict__ onrm, float* __restrict__ cull) {
+                       float4* __restrict__ onrm, float* __restrict__ cull, float4* __restrict__ ball) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   geo[i] = make_float4(p[3 * i], p[3 * i + 1], p[3 * i + 2], r[i]);
@@ -1448,7 +1538,10 @@ __global__ void k_prep(const float* __restrict__ p, const float* __restrict__ r,
   const float inv = 1.0f / sqrtf(nx * nx + ny * ny + nz * nz);
   const float sigma = sigma_scale * softplus_f(lam[i]);
   onrm[i] = make_float4(nx * inv, ny * inv, nz * inv, sigma);
-  if (!(sigma > 0.0f)) cull[i] = -1.0f;
+  if (!(sigma > 0.0f)) {
+    cull[i] = -1.0f;
+    ball[i].w = -1.0f;
+  }
 }
 
 // out: [hidden, overflow, over-vertices, over-planes, over-work, over-stack]
@@ -1518,7 +1611,7 @@ pf_status connect_loss_impl(const Scene& sc, float lambda, const pf_grads& g, do
 }
 
 void free_scene(Scene* sc, hipStream_t s, bool async) {
-  void* ptrs[] = {sc->geo,  sc->nrm,    sc->cull,   sc->flags, sc->row,  sc->nrast, sc->col,
+  void* ptrs[] = {sc->geo,  sc->nrm,    sc->cull, sc->ball,   sc->flags, sc->row,  sc->nrast, sc->col,
                   sc->plane, sc->t_sp, sc->t_sidx, sc->t_srad, sc->t_lo, sc->t_hi, sc->wit, sc->tri};
   // synchronous: renders on any stream may still read the arrays
   if (!async) (void)hipDeviceSynchronize();
@@ -1526,6 +1619,7 @@ void free_scene(Scene* sc, hipStream_t s, bool async) {
     if (q) pf::pool_free(q, async ? s : nullptr);
   sc->geo = sc->nrm = nullptr;
   sc->cull = nullptr;
+  sc->ball = nullptr;
   sc->flags = sc->row = sc->nrast = sc->col = nullptr;
   sc->plane = nullptr;
   sc->t_sp = sc->t_lo = sc->t_hi = nullptr;
@@ -1650,6 +1744,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
 
   // per-cell clipping
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->cull, sizeof(float) * n, s));
+  PF_HIP_TRY(pf::pool_alloc((void**)&sc->ball, sizeof(float4) * n, s));
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->flags, sizeof(int32_t) * n, s));
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->wit, sizeof(int32_t) * WIT * n, s));
   PF_HIP_TRY(hipMemsetAsync(sc->wit, 0xFF, sizeof(int32_t) * WIT * n, s));
@@ -1707,7 +1802,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
     {
       ProfScope ps("k_witness", s);
       k_witness<<<g256, 256, 0, s>>>(sp.p, sidx.p, spos.p, n, bmin, bmax, warm_wit, sc->wit, counts.p, sc->nrast,
-                                     sc->cull, sc->flags, keep.p);
+                                     sc->cull, sc->ball, sc->flags, keep.p);
     }
     PF_HIP_TRY(hipGetLastError());
     PF_HIP_TRY(exclusive_scan_u32(keep.p, keep_pos.p, n, n_keep.p, s));
@@ -1741,7 +1836,8 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
     k_clip<2, FACE_CAP, 0><<<(unsigned)used.n, 64, 0, s>>>(used.sp, used.sidx, used.n, used.lo, used.hi, used.lv, bmin,
                                                            bmax, prm.radius, nullptr, nullptr, faces_tmp.p, nullptr,
                                                            counts.p, sc->nrast, sc->cull, sc->flags, warm_row,
-                                                           warm_col, warm_tri, warm_wit, sp.p, spos.p, n, sc->wit);
+                                                           warm_col, warm_tri, warm_wit, sp.p, spos.p, n, sc->wit,
+                                                           prm.normal, prm.tex, sc->ball);
   }
   PF_HIP_TRY(hipGetLastError());
   // second pass (twice the capacity, edge table still in LDS) for the cells
@@ -1761,7 +1857,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
       k_clip<SPL_MID, PM_MID, 1><<<nbig, 64, 0, s>>>(used.sp, used.sidx, used.n, used.lo, used.hi, used.lv, bmin, bmax,
                                                     prm.radius, klist.p, nullptr, faces_big.p, bigslot.p, counts.p,
                                                     sc->nrast, sc->cull, sc->flags, warm_row, warm_col, warm_tri, warm_wit,
-                                                    sp.p, spos.p, n, sc->wit);
+                                                    sp.p, spos.p, n, sc->wit, prm.normal, prm.tex, sc->ball);
     }
     PF_HIP_TRY(hipGetLastError());
     unsigned int nbig3 = 0;
@@ -1773,7 +1869,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
       k_clip<SPL_BIG, PM_BIG, 2><<<nbig3, 64, 0, s>>>(used.sp, used.sidx, used.n, used.lo, used.hi, used.lv, bmin, bmax,
                                                      prm.radius, klist.p, eo_big.p, faces_big.p, bigslot.p, counts.p,
                                                      sc->nrast, sc->cull, sc->flags, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                     nullptr, 0, sc->wit);
+                                                     nullptr, 0, sc->wit, prm.normal, prm.tex, sc->ball);
       PF_HIP_TRY(hipGetLastError());
     }
   }
@@ -1790,7 +1886,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
   }
 
   k_prep<<<g256, 256, 0, s>>>(prm.p, prm.radius, prm.normal, prm.occ_logit, prm.sigma_scale, n, sc->geo,
-                              sc->nrm, sc->cull);
+                              sc->nrm, sc->cull, sc->ball);
   PF_HIP_TRY(hipGetLastError());
   DevBuf<unsigned long long> cnt(s);
   PF_HIP_TRY(cnt.alloc(6));

@@ -47,6 +47,8 @@ struct Scene {
   float4* nrm = nullptr;           // (unit normal, sigma)
   float* cull = nullptr;           // radius of a ball at p bounding the
                                    // non-empty bounded cell; < 0: hidden
+  float4* ball = nullptr;          // centre and radius of a ball around the dense part of the
+                                   // bounded cell; radius < 0: none (never rendered)
   int32_t* flags = nullptr;
   int32_t* wit = nullptr;          // [n][8] per empty cell: planes that prove it empty, recent planes (pf_build.hip)
   // adjacency, CSR; per cell: raster faces, other neighbour faces, box faces

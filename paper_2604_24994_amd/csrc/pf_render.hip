@@ -2,7 +2,7 @@
 //
 // Raster, per view (Sec. 3.2, rasterization; appendix B order):
 //   k_view_count  per cell: power distance from the camera centre (the sort
-//                 key) and the tile rectangle of its cull ball
+//                 key) and the tile rectangle of its ball
 //   scan          cell offsets into the pair list
 //   k_view_emit   (tile, key<<32 | cell) pairs + tile histogram
 //   scan/scatter  counting sort by tile
@@ -34,6 +34,8 @@ __device__ inline uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+
+constexpr double RECT_PAD = 1e-2;   // pixels
 
 // Tile rectangle of a ball (camera-space centre X,Y,Z, radius rho).
 __device__ bool ball_rect(const pf_camera& c, double X, double Y, double Z, double rho, int tiles_x, int tiles_y,
@@ -103,10 +105,11 @@ __device__ bool ball_rect(const pf_camera& c, double X, double Y, double Z, doub
     y0 = 0; y1 = tiles_y - 1;
     return true;
   }
-  // pixels whose centre (p + 1/2) may lie in [lo, hi], padded by one pixel
-  const double pxl = ceil(ulo - 0.5) - 1.0, pxh = floor(uhi - 0.5) + 1.0;
-  const double pyl = ceil(vlo - 0.5) - 1.0, pyh = floor(vhi - 0.5) + 1.0;
-  if (!(pxh >= 0.0 && pyh >= 0.0 && pxl <= W - 1 && pyl <= H - 1)) return false;
+  // pixels whose centre (p + 1/2) may lie in [lo, hi] (a ball between two pixel
+  // centres has none); the pad covers the rounding of the float64 bounds
+  const double pxl = ceil(ulo - 0.5 - RECT_PAD), pxh = floor(uhi - 0.5 + RECT_PAD);
+  const double pyl = ceil(vlo - 0.5 - RECT_PAD), pyh = floor(vhi - 0.5 + RECT_PAD);
+  if (!(pxh >= 0.0 && pyh >= 0.0 && pxl <= W - 1 && pyl <= H - 1 && pxl <= pxh && pyl <= pyh)) return false;
   x0 = (int)fmax(0.0, floor(fmax(pxl, 0.0) / TILE));
   x1 = (int)fmin((double)(tiles_x - 1), floor(fmin(pxh, W - 1) / TILE));
   y0 = (int)fmax(0.0, floor(fmax(pyl, 0.0) / TILE));
@@ -148,18 +151,18 @@ __device__ inline bool cone_tile(const pf_camera& c, const Cone& k, int tx, int 
   return k.cmin >= 0.0 ? (dot >= 0.0 && dot * dot >= k.cmin * k.cmin * d2) : (dot * dot <= k.cmin * k.cmin * d2);
 }
 
-// Tile footprint of a cell's cull ball in a view: 0 none, 1 the rectangle
+// Tile footprint of a cell's ball in a view: 0 none, 1 the rectangle
 // [x0, x1] x [y0, y1], 2 the tiles of that rectangle (all of the view)
 // accepted by cone_tile(k).
-__device__ inline int cell_rect(const ViewArgs& v, const float4 g, float rho, int& x0, int& x1, int& y0, int& y1,
+__device__ inline int cell_rect(const ViewArgs& v, const float4 g, int& x0, int& x1, int& y0, int& y1,
                                 Cone& k) {
-  if (!(rho >= 0.0f)) return 0;
+  if (!(g.w >= 0.0f)) return 0;
   const float* m = v.cam.c2w;
   const double ex = (double)g.x - m[3], ey = (double)g.y - m[7], ez = (double)g.z - m[11];
   const double X = m[0] * ex + m[4] * ey + m[8] * ez;
   const double Y = m[1] * ex + m[5] * ey + m[9] * ez;
   const double Z = m[2] * ex + m[6] * ey + m[10] * ez;
-  const double r = (double)rho * (1.0 + 1e-5) + 1e-7;
+  const double r = (double)g.w * (1.0 + 1e-5) + 1e-7;
   if (!ball_rect(v.cam, X, Y, Z, r, v.tiles_x, v.tiles_y, x0, x1, y0, y1)) return 0;
   if (v.cam.model == 0 && Z - r <= 1e-9 * (1.0 + fabs(Z))) {
     const double L = sqrt(X * X + Y * Y + Z * Z);
@@ -181,7 +184,7 @@ __device__ inline int cell_rect(const ViewArgs& v, const float4 g, float rho, in
 // Cells whose footprint needs the per-tile cone test are listed in
 // cone_list (as view * n + cell) and counted by k_cone_count.
 __global__ void k_view_count(const ViewDev* __restrict__ views, const float4* __restrict__ geo,
-                             const float* __restrict__ cull, const float* __restrict__ power, int64_t n,
+                             const float4* __restrict__ ball, const float* __restrict__ power, int64_t n,
                              uint32_t* __restrict__ cnt, uint32_t* __restrict__ key, uint32_t* __restrict__ cone_list,
                              uint32_t* __restrict__ cone_n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -192,7 +195,7 @@ __global__ void k_view_count(const ViewDev* __restrict__ views, const float4* __
   int x0, x1, y0, y1;
   Cone k;
   uint32_t c = 0;
-  const int mode = cell_rect(v, g, cull[i], x0, x1, y0, y1, k);
+  const int mode = cell_rect(v, ball[i], x0, x1, y0, y1, k);
   if (mode == 1) {
     c = (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
   } else if (mode == 2) {
@@ -210,8 +213,7 @@ __global__ void k_view_count(const ViewDev* __restrict__ views, const float4* __
 // so that a cell whose footprint covers many tiles is spread over the wave
 // rather than holding it, and the stores of a step are contiguous.  A
 // cell's pairs keep the order of its rectangle (rows of tiles, then tiles).
-__global__ void __launch_bounds__(256) k_view_emit(const ViewDev* __restrict__ views, const float4* __restrict__ geo,
-                                                   const float* __restrict__ cull, int64_t n,
+__global__ void __launch_bounds__(256) k_view_emit(const ViewDev* __restrict__ views, const float4* __restrict__ ball, int64_t n,
                                                    const uint32_t* __restrict__ off, const uint32_t* __restrict__ key,
                                                    uint32_t* __restrict__ ptile, unsigned long long* __restrict__ pval,
                                                    uint32_t* __restrict__ tile_cnt) {
@@ -228,7 +230,7 @@ __global__ void __launch_bounds__(256) k_view_emit(const ViewDev* __restrict__ v
   if (i < n) {
     const int64_t oi = (int64_t)blockIdx.y * n + i;
     Cone k;
-    const int mode = cell_rect(vd.v, geo[i], cull[i], x0, x1, y0, y1, k);
+    const int mode = cell_rect(vd.v, ball[i], x0, x1, y0, y1, k);
     if (mode == 1) {   // (cone footprints: k_cone_emit)
       nt = (x1 - x0 + 1) * (y1 - y0 + 1);
       o = off[oi];
@@ -274,8 +276,8 @@ __global__ void __launch_bounds__(256) k_view_emit(const ViewDev* __restrict__ v
 // One workgroup per listed (view, cell): its threads test the tiles of the
 // view in parallel.
 __global__ void __launch_bounds__(256) k_cone_count(const ViewDev* __restrict__ views,
-                                                    const float4* __restrict__ geo, const float* __restrict__ cull,
-                                                    int64_t n, const uint32_t* __restrict__ cone_list,
+                                                    const float4* __restrict__ ball, int64_t n,
+                                                    const uint32_t* __restrict__ cone_list,
                                                     uint32_t* __restrict__ cnt) {
   __shared__ uint32_t part[4];
   const uint32_t o = cone_list[blockIdx.x];
@@ -283,7 +285,7 @@ __global__ void __launch_bounds__(256) k_cone_count(const ViewDev* __restrict__ 
   const ViewArgs& v = views[o / (uint64_t)n].v;
   int x0, x1, y0, y1;
   Cone k;
-  (void)cell_rect(v, geo[i], cull[i], x0, x1, y0, y1, k);
+  (void)cell_rect(v, ball[i], x0, x1, y0, y1, k);
   const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
   uint32_t c = 0;
   for (int t = threadIdx.x; t < nt; t += 256) c += cone_tile(v.cam, k, x0 + t % tw, y0 + t / tw) ? 1u : 0u;
@@ -293,8 +295,7 @@ __global__ void __launch_bounds__(256) k_cone_count(const ViewDev* __restrict__ 
   if (threadIdx.x == 0) cnt[o] = part[0] + part[1] + part[2] + part[3];
 }
 
-__global__ void __launch_bounds__(256) k_cone_emit(const ViewDev* __restrict__ views, const float4* __restrict__ geo,
-                                                   const float* __restrict__ cull, int64_t n,
+__global__ void __launch_bounds__(256) k_cone_emit(const ViewDev* __restrict__ views, const float4* __restrict__ ball, int64_t n,
                                                    const uint32_t* __restrict__ off, const uint32_t* __restrict__ key,
                                                    const uint32_t* __restrict__ cone_list,
                                                    uint32_t* __restrict__ ptile, unsigned long long* __restrict__ pval,
@@ -305,7 +306,7 @@ __global__ void __launch_bounds__(256) k_cone_emit(const ViewDev* __restrict__ v
   const ViewDev& vd = views[o / (uint64_t)n];
   int x0, x1, y0, y1;
   Cone k;
-  (void)cell_rect(vd.v, geo[i], cull[i], x0, x1, y0, y1, k);
+  (void)cell_rect(vd.v, ball[i], x0, x1, y0, y1, k);
   const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
   const unsigned long long val = ((unsigned long long)key[o] << 32) | (uint32_t)i;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -390,7 +391,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_tile_sort(unsigned long long* 
 struct SceneDev {
   const float4* geo;
   const float4* nrm;
-  const float* cull;
+  const float4* ball;
   const int32_t* row;
   const int32_t* nrast;
   const int32_t* col;
@@ -399,6 +400,21 @@ struct SceneDev {
   const float* tex;
   float tau;
 };
+
+// A cell's ball relative to the camera centre, its radius widened by what the
+// float32 test below can be off (a few 1e-7 of the centre's distance).
+__device__ inline float4 ball_from(const float4 ball, double ox, double oy, double oz) {
+  const float x = (float)((double)ball.x - ox), y = (float)((double)ball.y - oy), z = (float)((double)ball.z - oz);
+  return make_float4(x, y, z, ball.w + 1e-6f * (fabsf(x) + fabsf(y) + fabsf(z)));
+}
+
+// Whether the ray meets the ball's line of sight (the line through the camera
+// centre): squared distance of the centre from the line below the radius'.
+__device__ inline bool ball_hit(const RayD& R, const float4 b) {
+  const float t = b.x * R.fx + b.y * R.fy + b.z * R.fz;
+  const float qx = fmaf(-t, R.fx, b.x), qy = fmaf(-t, R.fy, b.y), qz = fmaf(-t, R.fz, b.z);
+  return qx * qx + qy * qy + qz * qz < b.w * b.w;
+}
 
 constexpr int RB = 256;     // tile-list entries staged in LDS per batch
 constexpr int RBLK = 256;   // record slots reserved per wave at a time
@@ -502,20 +518,17 @@ __device__ inline float wave_add_f(float x) {
   return x;
 }
 
-// Cone around the rays of a wave's 8x8 pixels (camera centre o, unit axis a,
-// half-angle with cosine ct and sine st).  A cell's ball can only be met by
+// Cone around the rays of a wave's 8x8 pixels (unit axis a, half-angle with
+// cosine ct and sine st; the apex is the camera centre).  A cell's ball can only be met by
 // one of those rays if it reaches the cone, which ray_cone_meets tests for
 // 64 cells at a time, one per lane; the exact per-pixel test follows for
 // the cells that pass, so the test only has to err on the side of passing.
 struct RayCone {
-  float ox, oy, oz, ax, ay, az, ct, st;
+  float ax, ay, az, ct, st;
 };
 
 __device__ inline RayCone ray_cone(const RayD& R, bool use) {
   RayCone C;
-  C.ox = (float)R.ox;   // (float32 values)
-  C.oy = (float)R.oy;
-  C.oz = (float)R.oz;
   const float sx = wave_add_f(use ? R.fx : 0.0f), sy = wave_add_f(use ? R.fy : 0.0f),
               sz = wave_add_f(use ? R.fz : 0.0f);
   const float n2 = sx * sx + sy * sy + sz * sz;
@@ -535,19 +548,17 @@ __device__ inline RayCone ray_cone(const RayD& R, bool use) {
   return C;
 }
 
-// Whether the ball (x, y, z, radius rho) may reach the cone: the distance of
-// its centre from the cone's surface, |c x a| ct - (c.a) st with c the centre
+// Whether the ball b (ball_from) may reach the cone: the distance of its centre from the cone's surface, |c x a| ct - (c.a) st with c the centre
 // relative to the apex, is at most rho (it is negative inside; a centre
 // nearer to the apex than to the surface is further away than that).  The
-// margin covers the rounding of c and of the products (a few 1e-7 |c|).
-__device__ inline bool ray_cone_meets(const RayCone& C, float x, float y, float z, float rho) {
+// margin covers the rounding of the products (a few 1e-7 |c|).
+__device__ inline bool ray_cone_meets(const RayCone& C, const float4 b) {
   if (C.st > 1.0f) return true;
-  const float cx = x - C.ox, cy = y - C.oy, cz = z - C.oz;
-  const float par = cx * C.ax + cy * C.ay + cz * C.az;
-  const float ux = cy * C.az - cz * C.ay, uy = cz * C.ax - cx * C.az, uz = cx * C.ay - cy * C.ax;
+  const float par = b.x * C.ax + b.y * C.ay + b.z * C.az;
+  const float ux = b.y * C.az - b.z * C.ay, uy = b.z * C.ax - b.x * C.az, uz = b.x * C.ay - b.y * C.ax;
   const float perp = fsqrt(ux * ux + uy * uy + uz * uz);
-  const float far = fabsf(cx) + fabsf(cy) + fabsf(cz) + fabsf(C.ox) + fabsf(C.oy) + fabsf(C.oz);
-  return !(perp * C.ct - par * C.st > rho * (1.0f + 1e-5f) + 4e-6f * far + 1e-7f);
+  const float far = fabsf(b.x) + fabsf(b.y) + fabsf(b.z);
+  return !(perp * C.ct - par * C.st > b.w * (1.0f + 1e-5f) + 2e-6f * far + 1e-7f);
 }
 
 // Pixels of a wave as points u = (d.b1, d.b2) / (d.a) of the plane at unit
@@ -574,12 +585,10 @@ __device__ inline RayGrid ray_grid(const RayD& R, const RayCone& C, bool use, fl
 }
 
 // Whether the ball may meet one of the rays u[0..63] (pairs of points).
-__device__ inline bool ray_grid_meets(const RayCone& C, const RayGrid& G, const float4* u2, float x, float y, float z,
-                                      float rho) {
+__device__ inline bool ray_grid_meets(const RayCone& C, const RayGrid& G, const float4* u2, const float4 b) {
   if (C.st > 1.0f) return true;
-  const float cx = x - C.ox, cy = y - C.oy, cz = z - C.oz;
-  const float far = fabsf(cx) + fabsf(cy) + fabsf(cz) + fabsf(C.ox) + fabsf(C.oy) + fabsf(C.oz);
-  const float r = rho * (1.0f + 1e-5f) + 4e-6f * far + 1e-7f;
+  const float cx = b.x, cy = b.y, cz = b.z;
+  const float r = b.w * (1.0f + 1e-5f) + 2e-6f * (fabsf(cx) + fabsf(cy) + fabsf(cz)) + 1e-7f;
   const float depth = cx * C.ax + cy * C.ay + cz * C.az;
   if (!(depth > 2.0f * r)) return true;   // around or behind the camera
   const float inv = 1.0f / depth;
@@ -767,7 +776,7 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
   __shared__ int s_ci[RB];
   __shared__ float4 s_geo[RB];
   __shared__ float4 s_nrm[RB];
-  __shared__ float s_rho[RB];
+  __shared__ float4 s_ball[RB];   // ball_from
   __shared__ int s_row[RB];
   __shared__ int s_nr[RB];
   __shared__ int s_more[4];
@@ -810,7 +819,7 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
         s_ci[threadIdx.x] = c;
         s_geo[threadIdx.x] = S.geo[c];
         s_nrm[threadIdx.x] = S.nrm[c];
-        s_rho[threadIdx.x] = S.cull[c];
+        s_ball[threadIdx.x] = ball_from(S.ball[c], R.ox, R.oy, R.oz);
         s_row[threadIdx.x] = S.row[c];
         s_nr[threadIdx.x] = S.nrast[c];
       }
@@ -825,18 +834,13 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
       {
         const RayCone cone = s_cone[wave];
         const int q = k0 + lane;
-        const float4 g = s_geo[q];
-        const float rho = s_rho[q];
-        todo = __ballot(q < nb && rho >= 0.0f && ray_cone_meets(cone, g.x, g.y, g.z, rho));
+        todo = __ballot(q < nb && ray_cone_meets(cone, s_ball[q]));
       }
       for (; todo; todo &= todo - 1) {
         if (!__any(live)) break;
         const int q = k0 + __ffsll((long long)todo) - 1;
         const int ci = __builtin_amdgcn_readfirstlane(s_ci[q]);
-        const float4 g = s_geo[q];
-        const float rho = s_rho[q];
-        const Local L = make_local(R, g.x, g.y, g.z);
-        const bool hit = live && (L.qq < (double)rho * (double)rho);
+        const bool hit = live && ball_hit(R, s_ball[q]);
         if constexpr (COUNT) {
           N.test += (unsigned long long)__popcll(__ballot(live));
           N.hit += (unsigned long long)__popcll(__ballot(hit));
@@ -844,11 +848,13 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
         }
         if (!__any(hit)) continue;
         if constexpr (COUNT) ++N.step_hit;
+        const float4 g = s_geo[q];
         const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
         Piece P;
         P.alpha = 0.0f;
         float r = 0.0f, gg = 0.0f, b = 0.0f;
         if (hit) {
+          const Local L = make_local(R, g.x, g.y, g.z);
           P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(s_row[q])),
                              __builtin_amdgcn_readfirstlane(s_nr[q]), s_nrm[q], tx, S.tau);
           if (P.alpha > 0.0f)
@@ -940,7 +946,7 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
   __shared__ int q_ci[CH];
   __shared__ float4 q_geo[CH];
   __shared__ float4 q_nrm[CH];
-  __shared__ float q_rho[CH];
+  __shared__ float4 q_ball[CH];   // ball_from
   __shared__ int q_row[CH];
   __shared__ int q_nr[CH];
   __shared__ float4 s_res[RING][64];               // (alpha, colour) per pixel
@@ -1001,21 +1007,20 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
     auto cull = [&](uint32_t b0) -> int {
       const uint32_t e = b0 + threadIdx.x;
       int c = -1;
-      float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      float rho = -1.0f;
+      float4 bl = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
       if (e < e1) {
         c = (int)(uint32_t)list[e];
-        g = S.geo[c];
-        rho = S.cull[c];
+        bl = ball_from(S.ball[c], R.ox, R.oy, R.oz);
       }
       const RayCone cone = s_cone;
-      bool keep = rho >= 0.0f && ray_cone_meets(cone, g.x, g.y, g.z, rho);
-      if (keep) keep = ray_grid_meets(cone, s_grid, s_u2, g.x, g.y, g.z, rho);
+      bool keep = c >= 0 && ray_cone_meets(cone, bl);
+      if (keep) keep = ray_grid_meets(cone, s_grid, s_u2, bl);
       const uint64_t km = __ballot(keep);
       if (lane == 0) s_cnt[wave] = __popcll(km);
-      float4 nr4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f), nr4 = g;
       int row = 0, nrast = 0;
       if (keep) {
+        g = S.geo[c];
         nr4 = S.nrm[c];
         row = S.row[c];
         nrast = S.nrast[c];
@@ -1032,7 +1037,7 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
         q_ci[at] = c;
         q_geo[at] = g;
         q_nrm[at] = nr4;
-        q_rho[at] = rho;
+        q_ball[at] = bl;
         q_row[at] = row;
         q_nr[at] = nrast;
       }
@@ -1109,13 +1114,11 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
           if (j >= nq) break;
           const int ci = __builtin_amdgcn_readfirstlane(q_ci[j]);
           const float4 g = q_geo[j];
-          const float rho = q_rho[j];
           // (pixels only leave the set, so an older value costs work, not results)
           const uint64_t lm = bcast64(
               __hip_atomic_load(&s_live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
           if (!lm) break;
-          const Local L = make_local(R, g.x, g.y, g.z);
-          const bool hit = ((lm >> lane) & 1ull) && (L.qq < (double)rho * (double)rho);
+          const bool hit = ((lm >> lane) & 1ull) && ball_hit(R, q_ball[j]);
           if constexpr (COUNT) {
             const uint64_t hm = __ballot(hit);
             N.test += (unsigned long long)__popcll(lm);
@@ -1127,6 +1130,7 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
           P.alpha = 0.0f;
           float r = 0.0f, gg = 0.0f, b = 0.0f;
           if (hit) {
+            const Local L = make_local(R, g.x, g.y, g.z);
             const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
             P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(q_row[j])),
                                      __builtin_amdgcn_readfirstlane(q_nr[j]), q_nrm[j], tx, S.tau);
@@ -1292,11 +1296,11 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
       const float4 g = S.geo[cell];
       const Local L = make_local(R, g.x, g.y, g.z);
       // contribution of this cell (identical code to the rasteriser)
-      const float rho = S.cull[cell];
+      const float4 bl = S.ball[cell];
       bool contrib = false;
       Piece P;
       float r = 0.0f, gg = 0.0f, b = 0.0f;
-      if (rho >= 0.0f && L.qq < (double)rho * (double)rho) {
+      if (bl.w >= 0.0f && ball_hit(R, ball_from(bl, R.ox, R.oy, R.oz))) {
         const float* tx = S.tex + (int64_t)cell * (KD * TEXW);
         const int r0 = S.row[cell];
         P = piece_geometry<false>(R, L, g.w, S.plane + r0, S.nrast[cell], S.nrm[cell], tx, S.tau);
@@ -1414,7 +1418,7 @@ SceneDev scene_dev(const Scene& sc) {
   SceneDev d;
   d.geo = sc.geo;
   d.nrm = sc.nrm;
-  d.cull = sc.cull;
+  d.ball = sc.ball;
   d.row = sc.row;
   d.nrast = sc.nrast;
   d.col = sc.col;
@@ -1520,7 +1524,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   const dim3 g((unsigned)((n + 255) / 256), (unsigned)nv);
   {
     ProfScope ps("k_view_count", s);
-    k_view_count<<<g, 256, 0, s>>>(G.views.p, sc.geo, sc.cull, sc.prm.power, n, G.cnt.p, G.key.p, G.cone_list.p,
+    k_view_count<<<g, 256, 0, s>>>(G.views.p, sc.geo, sc.ball, sc.prm.power, n, G.cnt.p, G.key.p, G.cone_list.p,
                                    G.cone_n.p);
   }
   PF_HIP_TRY(hipGetLastError());
@@ -1528,7 +1532,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   PF_HIP_TRY(hipMemcpyAsync(&ncone, G.cone_n.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
   PF_HIP_TRY(hipStreamSynchronize(s));
   if (ncone) {
-    k_cone_count<<<ncone, 256, 0, s>>>(G.views.p, sc.geo, sc.cull, n, G.cone_list.p, G.cnt.p);
+    k_cone_count<<<ncone, 256, 0, s>>>(G.views.p, sc.ball, n, G.cone_list.p, G.cnt.p);
     PF_HIP_TRY(hipGetLastError());
   }
   PF_HIP_TRY(hipMemsetAsync(G.cnt.p + nvc, 0, sizeof(uint32_t), s));
@@ -1547,9 +1551,9 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   PF_HIP_TRY(hipMemsetAsync(G.fill.p, 0, sizeof(uint32_t) * ntiles, s));
   {
     ProfScope ps("k_view_emit", s);
-    k_view_emit<<<g, 256, 0, s>>>(G.views.p, sc.geo, sc.cull, n, G.off.p, G.key.p, G.ptile.p, G.pval.p, G.tcnt.p);
+    k_view_emit<<<g, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.ptile.p, G.pval.p, G.tcnt.p);
     if (ncone)
-      k_cone_emit<<<ncone, 256, 0, s>>>(G.views.p, sc.geo, sc.cull, n, G.off.p, G.key.p, G.cone_list.p, G.ptile.p,
+      k_cone_emit<<<ncone, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.cone_list.p, G.ptile.p,
                                         G.pval.p, G.tcnt.p);
   }
   PF_HIP_TRY(hipGetLastError());
