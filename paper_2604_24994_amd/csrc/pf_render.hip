@@ -857,10 +857,11 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
           const Local L = make_local(R, g.x, g.y, g.z);
           P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(s_row[q])),
                              __builtin_amdgcn_readfirstlane(s_nr[q]), s_nrm[q], tx, S.tau);
-          if (P.alpha > 0.0f)
-            radiance_wave(tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
         }
         const bool contrib = hit && P.alpha > 0.0f;
+        if (__any(contrib))
+          radiance_wave(S.tex + (int64_t)ci * (KD * TEXW), tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), contrib, P.ux, P.uy,
+                        R.fx, R.fy, R.fz, S.tau, r, gg, b);
         if constexpr (COUNT) {
           const uint64_t mc = __ballot(contrib);
           N.contrib += (unsigned long long)__popcll(mc);
@@ -1129,16 +1130,17 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
           Piece P;
           P.alpha = 0.0f;
           float r = 0.0f, gg = 0.0f, b = 0.0f;
+          const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
           if (hit) {
             const Local L = make_local(R, g.x, g.y, g.z);
-            const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
             P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(q_row[j])),
                                      __builtin_amdgcn_readfirstlane(q_nr[j]), q_nrm[j], tx, S.tau);
-            if (P.alpha > 0.0f)
-              radiance_wave(tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
           }
           const bool contrib = hit && P.alpha > 0.0f;
           const uint64_t m = __ballot(contrib);
+          if (m)
+            radiance_wave(S.tex + (int64_t)ci * (KD * TEXW), tx, uniform_ptr(S.rgb + 3 * (int64_t)ci), contrib, P.ux,
+                          P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
           const int slot = (base + j) % RING;
           if (!lds_wait(&s_done, base + j - RING + 1, &s_live)) break;
           if (contrib) {

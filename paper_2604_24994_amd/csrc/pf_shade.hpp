@@ -187,20 +187,24 @@ __device__ inline float softmax2_sum(const float (&z)[N], float (&p)[N], float* 
   return sum;
 }
 
+// a b + c d with one rounding less (written out where two kernels have to
+// agree to the last bit: the compiler may fuse either product).
+__device__ inline float dot2(float a, float b, float c, float d) { return fmaf(a, b, c * d); }
+
 // Soft-Voronoi weights over the K detail sites at face point u (Sec. 3.4,
 // Eq. svdisp / Eq. svrad).  The logits are shifted by tau*|u| and written as
 //   |u - s_k| - |u| = (|s_k|^2 - 2 u.s_k) / (|u - s_k| + |u|),
 // which keeps them accurate when u is far from the sites (grazing rays).
 template <typename FP>
 __device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w) {
-  const float un = fsqrt(ux * ux + uy * uy);
+  const float un = fsqrt(dot2(ux, ux, uy, uy));
   float mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < KD; ++k) {
     const float sx = tx[k * TEXW + 0], sy = tx[k * TEXW + 1];
     const float ex = ux - sx, ey = uy - sy;
-    const float dist = fsqrt(ex * ex + ey * ey);
-    const float num = sx * sx + sy * sy - 2.0f * (ux * sx + uy * sy);
+    const float dist = fsqrt(dot2(ex, ex, ey, ey));
+    const float num = fmaf(-2.0f, dot2(ux, sx, uy, sy), dot2(sx, sx, sy, sy));
     const float den = dist + un;
     const float e = den > 0.0f ? num * frcp(den) : 0.0f;
     w[k] = -tau * e;
@@ -388,18 +392,71 @@ __device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, V
   return P;
 }
 
+// A cell's Spherical-Voronoi axes and colours spread over the wave as the A
+// operands of 4x4x1 FP32 MFMAs (sixteen blocks of four rows, lane 4 b + i
+// holding row i of block b; every instruction broadcasts one block to all):
+// lane l of ax[c] holds component c of axis km = l (site km / 8, axis km % 8),
+// and lane l of col[v] component l % 4 of the colour of km = 16 v + l / 4, with
+// a one in the place of the fourth component.  All 64 lanes must take part.
+struct WaveTex {
+  float ax[3], col[4];
+};
+
+__device__ inline WaveTex wave_tex(const float* __restrict__ tx) {
+  const int lane = threadIdx.x & 63;
+  WaveTex W;
+  const float* a = tx + (lane >> 3) * TEXW + 3 + 3 * (lane & 7);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) W.ax[c] = a[c];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int km = 16 * v + (lane >> 2), c = lane & 3;
+    W.col[v] = c < 3 ? tx[(km >> 3) * TEXW + 3 + 3 * MA + 3 * (km & 7) + c] : 1.0f;
+  }
+  return W;
+}
+
+// Sums of site K's lobes for the lane's direction g = d log2(e), as
+// (sum_m e_m c_m, sum_m e_m), e_m = 2^(a_m . g).  The B operands and the
+// results have one pixel (record) per lane, as everywhere else, so both
+// contractions, 8 x 3 and 4 x 8 per lane, run on the matrix cores with the
+// same products and the same order of additions as multiply-adds in the lane.
+template <int K>
+__device__ inline vec4f wave_lobes(const WaveTex& W, float gx, float gy, float gz) {
+  const vec4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  vec4f l0 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[0], gx, zero, 4, 2 * K, 0);
+  vec4f l1 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[0], gx, zero, 4, 2 * K + 1, 0);
+  l0 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[1], gy, l0, 4, 2 * K, 0);
+  l1 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[1], gy, l1, 4, 2 * K + 1, 0);
+  l0 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[2], gz, l0, 4, 2 * K, 0);
+  l1 = __builtin_amdgcn_mfma_f32_4x4x1f32(W.ax[2], gz, l1, 4, 2 * K + 1, 0);
+  constexpr int B = 8 * (K & 1);   // block of the site's first colour
+  const float c = W.col[K >> 1];
+  vec4f s = zero;
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l0[0]), s, 4, B + 0, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l0[1]), s, 4, B + 1, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l0[2]), s, 4, B + 2, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l0[3]), s, 4, B + 3, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l1[0]), s, 4, B + 4, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l1[1]), s, 4, B + 5, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l1[2]), s, 4, B + 6, 0);
+  s = __builtin_amdgcn_mfma_f32_4x4x1f32(c, __builtin_amdgcn_exp2f(l1[3]), s, 4, B + 7, 0);
+  return s;
+}
+static_assert(KD == 8 && MA == 8, "wave_tex and wave_lobes: 64 site-axis pairs, two colour blocks of eight");
+
 // Radiance at texture point u for direction d: base colour plus the
-// soft-Voronoi blend of the detail sites' Spherical-Voronoi colours.
-// For the rasteriser (one cell per wave, texture in scalar registers): the
-// lobes are exponentiated in base 2 without the max shift;
-// if any site's sum leaves [2^-100, 2^100], the colour is evaluated again
-// with each site's logits shifted by their largest (as in softmax2_sum).
-// That rare pass runs over the sites in a loop that is not unrolled, so that
-// its texture reads are its own and the common pass holds no texture values
-// for it.
+// soft-Voronoi blend of the detail sites' Spherical-Voronoi colours, for the
+// rasteriser (one cell per wave; all lanes take part, those outside `on` get
+// an unspecified colour).  The lobes are exponentiated in base 2 without the
+// max shift; where a site's sum leaves [2^-100, 2^100], the colour is evaluated
+// again with each site's logits shifted by their largest (as in
+// softmax2_sum).  That rare pass runs over the sites in a loop that is not
+// unrolled, so that its texture reads are its own.
 template <typename FP>
-__device__ inline void radiance_wave(FP tx, FP rgb, float ux, float uy, float fx, float fy, float fz, float tau,
-                                     float& cr, float& cg, float& cb) {
+__device__ inline void radiance_wave(const float* __restrict__ tex, FP tx, FP rgb, bool on, float ux, float uy, float fx,
+                                     float fy, float fz, float tau, float& cr, float& cg, float& cb) {
+  const WaveTex W = wave_tex(tex);
   float w[KD];
   sv_weights(tx, ux, uy, tau, w);
   const float gx = fx * LOG2E_F, gy = fy * LOG2E_F, gz = fz * LOG2E_F;
@@ -407,25 +464,22 @@ __device__ inline void radiance_wave(FP tx, FP rgb, float ux, float uy, float fx
   cg = rgb[1];
   cb = rgb[2];
   bool in_range = true;
-#pragma unroll
-  for (int k = 0; k < KD; ++k) {
-    const FP t = tx + k * TEXW;
-    float sum = 0.0f, sr = 0.0f, sg = 0.0f, sb = 0.0f;
-#pragma unroll
-    for (int m = 0; m < MA; ++m) {
-      const float e = __builtin_amdgcn_exp2f(t[3 + 3 * m] * gx + t[4 + 3 * m] * gy + t[5 + 3 * m] * gz);
-      sum += e;
-      sr += e * t[3 + 3 * MA + 3 * m];
-      sg += e * t[4 + 3 * MA + 3 * m];
-      sb += e * t[5 + 3 * MA + 3 * m];
-    }
-    in_range = in_range && sum >= 0x1p-100f && sum <= 0x1p100f;
-    const float sc = w[k] * frcp(sum);
-    cr += sc * sr;
-    cg += sc * sg;
-    cb += sc * sb;
-  }
-  if (!in_range) {
+  auto add = [&](const vec4f s, float wk) {
+    in_range = in_range && s[3] >= 0x1p-100f && s[3] <= 0x1p100f;
+    const float sc = wk * frcp(s[3]);
+    cr += sc * s[0];
+    cg += sc * s[1];
+    cb += sc * s[2];
+  };
+  add(wave_lobes<0>(W, gx, gy, gz), w[0]);
+  add(wave_lobes<1>(W, gx, gy, gz), w[1]);
+  add(wave_lobes<2>(W, gx, gy, gz), w[2]);
+  add(wave_lobes<3>(W, gx, gy, gz), w[3]);
+  add(wave_lobes<4>(W, gx, gy, gz), w[4]);
+  add(wave_lobes<5>(W, gx, gy, gz), w[5]);
+  add(wave_lobes<6>(W, gx, gy, gz), w[6]);
+  add(wave_lobes<7>(W, gx, gy, gz), w[7]);
+  if (on && !in_range) {
     cr = rgb[0];
     cg = rgb[1];
     cb = rgb[2];
@@ -453,7 +507,6 @@ __device__ inline void radiance_wave(FP tx, FP rgb, float ux, float uy, float fx
     }
   }
 }
-
 
 // The same for the walk (a cell per lane, the texture read per lane): every softmax shifted by its largest logit, which keeps fewer values live
 // than the unshifted form with its rare shifted pass (the walk is held to 80
