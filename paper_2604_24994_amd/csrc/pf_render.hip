@@ -18,7 +18,8 @@
 // Trace, per view (Sec. 3.2, ray tracing; appendix C):
 //   k_start_*     argmin power distance from the camera centre
 //   k_trace       one lane per ray; per step the piece of the current cell
-//                 (same device code as the rasteriser) and the exit face
+//                 (same device code as the rasteriser) and the exit face in one
+//                 pass over its faces; colours evaluated for many rays at once
 #include "pf_internal.hpp"
 #include "pf_render.hpp"
 #include "pf_shade.hpp"
@@ -855,7 +856,7 @@ k_raster(const ViewDev* __restrict__ views, int nview, SceneDev S, const unsigne
         float r = 0.0f, gg = 0.0f, b = 0.0f;
         if (hit) {
           const Local L = make_local(R, g.x, g.y, g.z);
-          P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(s_row[q])),
+          P = piece_geometry(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(s_row[q])),
                              __builtin_amdgcn_readfirstlane(s_nr[q]), s_nrm[q], tx, S.tau);
         }
         const bool contrib = hit && P.alpha > 0.0f;
@@ -1133,7 +1134,7 @@ k_raster_split(const ViewDev* __restrict__ views, int nview, SceneDev S, const u
           const ufloat_p tx = uniform_ptr(S.tex + (int64_t)ci * (KD * TEXW));
           if (hit) {
             const Local L = make_local(R, g.x, g.y, g.z);
-            P = piece_geometry<true>(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(q_row[j])),
+            P = piece_geometry(R, L, g.w, uniform_ptr(S.plane + __builtin_amdgcn_readfirstlane(q_row[j])),
                                      __builtin_amdgcn_readfirstlane(q_nr[j]), q_nrm[j], tx, S.tau);
           }
           const bool contrib = hit && P.alpha > 0.0f;
@@ -1251,18 +1252,41 @@ __global__ void __launch_bounds__(256) k_start_final(const double* __restrict__ 
   if (threadIdx.x == 0) out[0] = (int32_t)si[0];
 }
 
-// STORE: every contribution is also written as a record (as the store-mode
-// rasteriser does) with a one-record segment; rec_seg must be zeroed by the
-// caller (unused slots of the wave's segment blocks keep an empty mask).
-// Six waves per SIMD (at most 80 VGPRs): the walk is bound by the latency of
-// its per-step gathers, and occupancy hides it (100 Mrays/s at the three
-// waves that 136 unconstrained VGPRs allow, 125 at six).
+// Face loads a ray of the walk has in flight (with four and with two, before
+// the radiance was deferred: 5.74 and 5.80 ms for 921600 rays of 67 cells in a
+// 1M-cell scene, 0.85 and 0.93 ms for a fisheye view of 16k cells).
+constexpr int WALK_FACES = 4;
+// Contributions a ray of the walk may have pending (of 6, 8, 10, 12 the ring of
+// ten was best or within 2% for both views: 4.5, 3.98, 3.96, 4.15 ms and 0.81,
+// 0.69, 0.68, 0.60 ms; sixteen, which leaves one wave per SIMD less, 5.2 and
+// 0.62 ms), and the ratio of what they cost: a ray-by-ray evaluation of all
+// pending rays takes about as long as twelve evaluations of one cell (ratio 4,
+// 8, 16, 32: 3.96, 3.84, 3.79, 3.74 ms and 0.68, 0.69, 0.70, 0.77 ms).
+constexpr int WALK_QUEUE = 10;
+constexpr int WALK_GROUP = 12;
+
+// One lane per ray.  STORE: every contribution is also written as a record (as
+// the store-mode rasteriser does) with a one-record segment; rec_seg must be
+// zeroed by the caller (unused slots of the wave's segment blocks keep an empty
+// mask).
+// A step reads every face of the cell once, for the piece and for the exit
+// together.  Opacity decides how far a ray goes, colour does not: a contribution's
+// texture point and weight wait in the ray's LDS ring until it is full.  Then
+// either all rays of the wave that hold that cell, now or some contributions
+// ago, are shaded at once on the matrix cores from one coalesced read of its
+// texture, or, where few do, every ray's oldest contribution with per-lane reads.
+// What bounds it are those gathers (a texture is 1.6 kB) and the latency of a
+// step's loads; the ring's LDS and the registers leave four waves per SIMD.
+// 921600 rays through 1M cells (67 cells, 18 faces each, 22 contributions per
+// ray): 8.9 ms with two face passes and the radiance in place, 5.7 ms with one,
+// 3.7 ms with the radiance deferred (1.9 ms of it the faces, 0.6 the opacity);
+// a 300 x 300 fisheye of 16k cells 1.48, 0.85 and 0.67 ms.
 // COUNT: the walk's work counters are added to counters[0..5]
 // (TRACE_COUNTERS): rays walked, cells walked, pieces computed (sphere
 // hits), contributions, exit faces scanned, and the most cells one ray
 // walked (maximum).
 template <bool STORE, bool COUNT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 6)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ start,
                                                float t_min, int max_steps, float* __restrict__ rgba,
                                                unsigned long long* __restrict__ truncated, int view,
@@ -1281,7 +1305,7 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
   int prev = -1;
   double t_cur = 0.0;
   bool cut = false;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int pix = py * v.cam.width + px;
   int head = -1;
@@ -1292,29 +1316,119 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
   unsigned long long n_pieces = 0, n_contrib = 0, n_faces = 0;
   int n_steps = 0;
   const bool walked = live && cell >= 0;
-  if (live && cell >= 0) {
-    int step = 0;
-    for (; step < max_steps; ++step) {
+  // contributions whose radiance is still to be evaluated, a ring per ray with
+  // holes: bit d of `held` marks slot d, `slot` is the next one
+  __shared__ float4 s_pend[4][WALK_QUEUE][64];             // cell, texture point, weight
+  __shared__ int s_rec[4][STORE ? WALK_QUEUE : 1][64];     // STORE: its record, or -1
+  unsigned held = 0;
+  int slot = 0;
+  // adds the colour of slot d's contribution
+  auto add = [&](int d, float wgt, float r, float gg, float b) {
+    cr = fmaf(wgt, r, cr);
+    cg = fmaf(wgt, gg, cg);
+    cb = fmaf(wgt, b, cb);
+    held &= ~(1u << d);
+    if constexpr (STORE) {
+      const int rec = s_rec[wave][d][lane];
+      if (rec >= 0) {
+        float* o = reinterpret_cast<float*>(rec_rf + rec);
+        o[1] = r;
+        o[2] = gg;
+        o[3] = b;
+      }
+    }
+  };
+  // evaluates pending contributions, among them the oldest of the first ray
+  // in `due` (a wave-uniform mask of rays that hold one)
+  auto shade = [&](uint64_t due) {
+    // the ray's oldest pending contribution
+    const unsigned rot = (held >> slot) | (held << (WALK_QUEUE - slot));
+    int d = slot + (rot ? __ffs((int)rot) - 1 : 0);
+    d = d < WALK_QUEUE ? d : d - WALK_QUEUE;
+    const float4 own = s_pend[wave][d][lane];
+    const int c = __builtin_amdgcn_readlane(__float_as_int(own.x), __ffsll((long long)due) - 1);
+    int dc = -1;
+#pragma unroll
+    for (int j = 0; j < WALK_QUEUE; ++j)
+      if ((held >> j & 1u) && __float_as_int(s_pend[wave][j][lane].x) == c) dc = j;
+    float r, gg, b;
+    if (WALK_GROUP * __popcll(__ballot(dc >= 0)) >= __popcll(__ballot(held != 0u))) {
+      const bool on = dc >= 0;
+      const float4 p = s_pend[wave][max(dc, 0)][lane];
+      const float ux = on ? p.y : 0.0f, uy = on ? p.z : 0.0f;
+      const float* tx = S.tex + (int64_t)c * (KD * TEXW);
+      radiance_wave(tx, uniform_ptr(tx), uniform_ptr(S.rgb + 3 * (int64_t)c), on, ux, uy, R.fx, R.fy, R.fz, S.tau, r,
+                    gg, b);
+      if (on) add(dc, p.w, r, gg, b);
+    } else if (held != 0u) {
+      const int own_c = __float_as_int(own.x);
+      radiance_lane(S.tex + (int64_t)own_c * (KD * TEXW), S.rgb + 3 * (int64_t)own_c, own.y, own.z, R.fx, R.fy, R.fz,
+                    S.tau, r, gg, b);
+      add(d, own.w, r, gg, b);
+    }
+  };
+  bool going = walked && max_steps > 0;
+  cut = walked && max_steps == 0;
+  int step = 0;
+  while (__any(going)) {
+    // every ray that goes on needs a free slot
+    uint64_t full;
+    while ((full = __ballot(going && (held >> slot & 1u))) != 0ull) {
+      shade(full);
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (going) {
+      going = false;   // set again where the walk goes on
       const float4 g = S.geo[cell];
       const Local L = make_local(R, g.x, g.y, g.z);
-      // contribution of this cell (identical code to the rasteriser)
       const float4 bl = S.ball[cell];
+      const int f0 = S.row[cell], nf = S.row[cell + 1] - f0;
+      const float* tx = S.tex + (int64_t)cell * (KD * TEXW);
+      // one pass over the faces clips the piece (the same arithmetic as the
+      // rasteriser's; raster faces come first) and finds the exit: the nearest
+      // face ahead of the current position that the ray leaves through, and the
+      // second nearest, which is the exit where the nearest is the face the ray
+      // came through (its neighbour is read for the winner alone)
+      const double D = (double)g.w * (double)g.w - L.qq;
+      const bool piece = D > 0.0 && bl.w >= 0.0f && ball_hit(R, ball_from(bl, R.ox, R.oy, R.oz));
+      const int nr = piece ? S.nrast[cell] : 0;
+      const float sq = piece ? fsqrt((float)D) : 0.0f;
+      Interval I = {-sq, sq, -1, -1};
+      const float s_cur = (float)(t_cur + L.b);
+      const float s_min = s_cur - 1e-6f * (1.0f + fabsf(s_cur));
+      const float nqx = -L.qx, nqy = -L.qy, nqz = -L.qz;
+      float best = INFINITY, second = INFINITY;
+      int bf = -1, sf = -1;
+      auto face = [&](const float4 pl, int f) {
+        const float a = face_slope(R, pl);
+        const float s = face_offset(pl, nqx, nqy, nqz) * frcp(a);
+        clip_face(I, a, s, f < nr, f);
+        const bool ahead = a > 0.0f && s >= s_min && f < nf;
+        const bool lt1 = ahead && s < best, lt2 = ahead && s < second;
+        second = lt1 ? best : (lt2 ? s : second);
+        sf = lt1 ? bf : (lt2 ? f : sf);
+        best = lt1 ? s : best;
+        bf = lt1 ? f : bf;
+      };
+      const float4* __restrict__ pf = S.plane + f0;
+      for (int f = 0; f < nf; f += WALK_FACES) {
+        float4 pl[WALK_FACES];
+#pragma unroll
+        for (int j = 0; j < WALK_FACES; ++j) pl[j] = pf[min(f + j, nf - 1)];
+#pragma unroll
+        for (int j = 0; j < WALK_FACES; ++j) face(pl[j], f + j);
+      }
       bool contrib = false;
       Piece P;
-      float r = 0.0f, gg = 0.0f, b = 0.0f;
-      if (bl.w >= 0.0f && ball_hit(R, ball_from(bl, R.ox, R.oy, R.oz))) {
-        const float* tx = S.tex + (int64_t)cell * (KD * TEXW);
-        const int r0 = S.row[cell];
-        P = piece_geometry<false>(R, L, g.w, S.plane + r0, S.nrast[cell], S.nrm[cell], tx, S.tau);
-        if (P.alpha > 0.0f) {
-          radiance_lane(tx, S.rgb + 3 * (int64_t)cell, P.ux, P.uy, R.fx, R.fy, R.fz, S.tau, r, gg, b);
-          contrib = true;
-        }
-        if constexpr (COUNT) {
-          ++n_pieces;
-          n_contrib += contrib ? 1ull : 0ull;
-        }
+      if (piece) {
+        P = piece_dense<false>(R, L, I, S.nrm[cell], tx, S.tau);
+        contrib = P.alpha > 0.0f;
       }
+      if constexpr (COUNT) {
+        n_pieces += (bl.w >= 0.0f && ball_hit(R, ball_from(bl, R.ox, R.oy, R.oz))) ? 1ull : 0ull;
+        n_contrib += contrib ? 1ull : 0ull;
+      }
+      int rec = -1;
       if constexpr (STORE) {
         const uint64_t m = __ballot(contrib);
         if (m) {
@@ -1333,13 +1447,13 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
             sleft = RBLK;
           }
           if (contrib) {
-            const long long slot = rblk + __popcll(m & lt), sg = sblk + __popcll(m & lt);
-            if (slot < rec_cap) {
-              rec_ri[slot] = make_int4(cell, pix, head, pack_view_bind(view, P.bind0, P.bind1));
-              rec_rf[slot] = make_float4(P.alpha, r, gg, b);
-              rec_rt[slot] = T;
-              head = (int)slot;
-              if (sg < seg_cap) rec_seg[sg] = make_int4(cell, (int)slot, 1, 0);   // mask 1: one record
+            const long long rs = rblk + __popcll(m & lt), sg = sblk + __popcll(m & lt);
+            if (rs < rec_cap) {
+              rec_ri[rs] = make_int4(cell, pix, head, pack_view_bind(view, P.bind0, P.bind1));
+              reinterpret_cast<float*>(rec_rf + rs)[0] = P.alpha;   // (the colour follows)
+              rec_rt[rs] = T;
+              head = rec = (int)rs;
+              if (sg < seg_cap) rec_seg[sg] = make_int4(cell, (int)rs, 1, 0);   // mask 1: one record
             }
           }
           rblk += cnt;
@@ -1349,40 +1463,62 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
         }
       }
       if (contrib) {
-        const float wgt = T * P.alpha;
-        cr += wgt * r;
-        cg += wgt * gg;
-        cb += wgt * b;
+        s_pend[wave][slot][lane] = make_float4(__int_as_float(cell), P.ux, P.uy, T * P.alpha);
+        if constexpr (STORE) s_rec[wave][slot][lane] = rec;
+        held |= 1u << slot;
+        slot = slot + 1 < WALK_QUEUE ? slot + 1 : 0;
         T *= (1.0f - P.alpha);
       }
-      if (T < t_min) break;
-      // exit: nearest face ahead of the current position that the ray leaves through
-      const float s_cur = (float)(t_cur + L.b);
-      const int f0 = S.row[cell], f1 = S.row[cell + 1];
-      if constexpr (COUNT) n_faces += (unsigned long long)(f1 - f0);
-      float best = INFINITY, best_any = INFINITY;
-      int bf = -1, bf_any = -1;
-      for (int f = f0; f < f1; ++f) {
-        const int nbr = S.col[f];
-        if (nbr == prev) continue;
-        const float4 pl = S.plane[f];
-        const float a = R.fx * pl.x + R.fy * pl.y + R.fz * pl.z;
-        if (!(a > 0.0f)) continue;
-        const float s = face_offset(pl, -L.qx, -L.qy, -L.qz) * frcp(a);
-        if (s < best_any) { best_any = s; bf_any = f; }
-        if (s >= s_cur - 1e-6f * (1.0f + fabsf(s_cur)) && s < best) { best = s; bf = f; }
+      bool on = !(T < t_min);
+      if (on) {
+        if constexpr (COUNT) n_faces += (unsigned long long)nf;
+        int nx = bf >= 0 ? S.col[f0 + bf] : prev;
+        if (nx == prev && sf >= 0) {
+          best = second;
+          bf = sf;
+          nx = S.col[f0 + bf];
+        }
+        if (nx == prev) {
+          // no such face: the full scan, which takes the nearest exit of all where
+          // none is ahead
+          best = INFINITY;
+          float best_any = INFINITY;
+          int bf_any = -1;
+          bf = -1;
+          for (int f = 0; f < nf; ++f) {
+            if (S.col[f0 + f] == prev) continue;
+            const float4 pl = pf[f];
+            const float a = face_slope(R, pl);
+            if (!(a > 0.0f)) continue;
+            const float s = face_offset(pl, nqx, nqy, nqz) * frcp(a);
+            if (s < best_any) { best_any = s; bf_any = f; }
+            if (s >= s_min && s < best) { best = s; bf = f; }
+          }
+          if (bf < 0) { bf = bf_any; best = best_any; }
+          nx = bf >= 0 ? S.col[f0 + bf] : -1;
+        }
+        on = bf >= 0;
+        if (on) {
+          t_cur = fmax(t_cur, (double)best - L.b);
+          on = nx >= 0;   // (else it left the domain box)
+        }
+        if (on) {
+          prev = cell;
+          cell = nx;
+          ++step;
+          going = step < max_steps;
+          cut = !going;
+        }
       }
-      if (bf < 0) { bf = bf_any; best = best_any; }
-      if (bf < 0) break;
-      t_cur = fmax(t_cur, (double)best - L.b);
-      const int nx = S.col[bf];
-      if (nx < 0) break;   // left the domain box
-      prev = cell;
-      cell = nx;
     }
-    cut = step == max_steps;
-    n_steps = step + (step < max_steps ? 1 : 0);
+    __builtin_amdgcn_wave_barrier();
   }
+  uint64_t rest;
+  while ((rest = __ballot(held != 0u)) != 0ull) {
+    shade(rest);
+    __builtin_amdgcn_wave_barrier();
+  }
+  n_steps = walked ? step + (step < max_steps ? 1 : 0) : 0;
   if (inside) {
     float* o = rgba + 4 * ((int64_t)py * v.cam.width + px);
     o[0] = cr;

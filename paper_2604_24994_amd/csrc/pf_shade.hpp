@@ -191,6 +191,12 @@ __device__ inline float softmax2_sum(const float (&z)[N], float (&p)[N], float* 
 // agree to the last bit: the compiler may fuse either product).
 __device__ inline float dot2(float a, float b, float c, float d) { return fmaf(a, b, c * d); }
 
+// a.b for the geometry of a piece, fused in a fixed order: a piece's ends, and
+// with them which rays graze it, must not depend on the kernel around it.
+__device__ inline float dot3(float ax, float ay, float az, float bx, float by, float bz) {
+  return fmaf(az, bz, fmaf(ax, bx, ay * by));
+}
+
 // Soft-Voronoi weights over the K detail sites at face point u (Sec. 3.4,
 // Eq. svdisp / Eq. svrad).  The logits are shifted by tau*|u| and written as
 //   |u - s_k| - |u| = (|s_k|^2 - 2 u.s_k) / (|u - s_k| + |u|),
@@ -254,92 +260,59 @@ struct Piece {
   float t1x, t1y, t1z, t2x, t2y, t2z;
 };
 
-// WAVE_CELL: every lane of the wave evaluates the same cell (the
-// rasteriser).  Its faces and texture are then read through the scalar
-// cache, the wave leaves the face loop as soon as no lane's interval is left,
-// and, before the displacement weights, it tests whether the dense part is
-// empty for every displacement the sites allow (for the walk's per-lane loads
-// that test costs more than it saves).  Either way alpha is the same.
-template <bool WAVE_CELL, typename VP, typename FP>
-__device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, VP faces, int nfaces, float4 nrm, FP tx,
-                                       float tau) {
+// A ray's interval within a cell while the faces clip it.
+struct Interval {
+  float s0, s1;
+  int b0, b1;
+};
+
+// Exit (a >= 0) and entry (a < 0) bounds of face f, met at s = offset / a, by
+// selects rather than branches.  a = d.m + 0 is never -0, so a face parallel
+// to the ray (a = +0) gives s = bb * (1/+0): -inf when the ray lies on its
+// outer side (bb < 0), which empties the interval, +inf (or NaN for bb = 0)
+// otherwise, which leaves it.  Once empty, an interval stays empty.
+__device__ inline void clip_face(Interval& I, float a, float s, bool on, int f) {
+  const bool exits = a >= 0.0f;
+  const bool out = on && exits && s < I.s1;
+  const bool in = on && !exits && s > I.s0;
+  I.s1 = out ? s : I.s1;
+  I.b1 = out ? f : I.b1;
+  I.s0 = in ? s : I.s0;
+  I.b0 = in ? f : I.b0;
+}
+
+// d.m + 0 of face plane (m, h) = pl.
+__device__ inline float face_slope(const RayD& R, const float4 pl) {
+  return fmaf(R.fz, pl.z, fmaf(R.fy, pl.y, R.fx * pl.x)) + 0.0f;
+}
+
+// The piece of an interval that the sphere and the faces have clipped.
+// WAVE_CELL: every lane of the wave evaluates the same cell (the rasteriser):
+// before the displacement weights, it tests whether the dense part is empty
+// for every displacement the sites allow (for the walk's per-lane loads that
+// test costs more than it saves).  Either way alpha is the same.
+template <bool WAVE_CELL, typename FP>
+__device__ inline Piece piece_dense(const RayD& R, const Local& L, Interval I, float4 nrm, FP tx, float tau) {
   Piece P;
   P.alpha = 0.0f;
   P.ux = P.uy = 0.0f;
-  P.bind0 = P.bind1 = -1;
-  const double D = (double)r * (double)r - L.qq;
-  P.s0 = 1.0f;
-  P.s1 = 0.0f;
-  if (D <= 0.0) return P;
-  const float sq = fsqrt((float)D);
-  float s0 = -sq, s1 = sq;
-  int b0 = -1, b1 = -1;
-  const float fx = R.fx, fy = R.fy, fz = R.fz;
-  // exit (a >= 0) and entry (a < 0) bounds by selects rather than branches.
-  // a = d.m + 0 is never -0, so a face parallel to the ray (a = +0) gives
-  // s = bb * (1/+0): -inf when the ray lies on its outer side (bb < 0),
-  // which empties the interval, +inf (or NaN for bb = 0) otherwise, which
-  // leaves it.  Once empty, an interval stays empty.
-  const float nqx = -L.qx, nqy = -L.qy, nqz = -L.qz;
-  auto clip = [&](const float4 pl, int f) {
-    const float a = (fx * pl.x + fy * pl.y + fz * pl.z) + 0.0f;
-    const float s = face_offset(pl, nqx, nqy, nqz) * frcp(a);
-    const bool exits = a >= 0.0f;
-    const bool out = exits && s < s1;
-    const bool in = !exits && s > s0;
-    s1 = out ? s : s1;
-    b1 = out ? f : b1;
-    s0 = in ? s : s0;
-    b0 = in ? f : b0;
-  };
-  if constexpr (WAVE_CELL) {
-    // two faces per step from one wave-uniform (scalar) address
-    int f = 0;
-    bool more = nfaces >= 2;
-    float4 c0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), c1 = c0;
-    if (more) {
-      c0 = load4(faces);
-      c1 = load4(faces + 1);
-    }
-    while (more) {
-      const float4 p0 = c0, p1 = c1;
-      const int fn = f + 2;
-      if (fn + 2 <= nfaces) {   // the next pair is loaded while this one is tested
-        const VP fp = faces + __builtin_amdgcn_readfirstlane(fn);
-        c0 = load4(fp);
-        c1 = load4(fp + 1);
-      }
-      clip(p0, f);
-      clip(p1, f + 1);
-      f = fn;
-      more = f + 2 <= nfaces && __any(s0 < s1);
-    }
-    if (f + 1 == nfaces) clip(load4(faces + __builtin_amdgcn_readfirstlane(f)), f);
-  } else {
-    // (the next face is loaded while this one is tested)
-    float4 nxt = nfaces > 0 ? load4(faces) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int f = 0; f < nfaces; ++f) {
-      const float4 pl = nxt;
-      if (f + 1 < nfaces) nxt = load4(faces + f + 1);
-      clip(pl, f);
-    }
-  }
-  if (L.beta > s0) { s0 = L.beta; b0 = -2; }
+  if (L.beta > I.s0) { I.s0 = L.beta; I.b0 = -2; }
+  const float s0 = I.s0, s1 = I.s1, fx = R.fx, fy = R.fy, fz = R.fz;
   P.s0 = s0;
   P.s1 = s1;
-  P.bind0 = b0;
-  P.bind1 = b1;
+  P.bind0 = I.b0;
+  P.bind1 = I.b1;
   if (!(s0 < s1)) return P;
 
   // dipole face with displacement (Sec. 3.3, Sec. 3.4)
   const float nx = nrm.x, ny = nrm.y, nz = nrm.z;
   onb(nx, ny, nz, P.t1x, P.t1y, P.t1z, P.t2x, P.t2y, P.t2z);
-  const float den = fx * nx + fy * ny + fz * nz;
-  const float qn = L.qx * nx + L.qy * ny + L.qz * nz;
-  const float qt1 = L.qx * P.t1x + L.qy * P.t1y + L.qz * P.t1z;
-  const float qt2 = L.qx * P.t2x + L.qy * P.t2y + L.qz * P.t2z;
-  const float dt1 = fx * P.t1x + fy * P.t1y + fz * P.t1z;
-  const float dt2 = fx * P.t2x + fy * P.t2y + fz * P.t2z;
+  const float den = dot3(fx, fy, fz, nx, ny, nz);
+  const float qn = dot3(L.qx, L.qy, L.qz, nx, ny, nz);
+  const float qt1 = dot3(L.qx, L.qy, L.qz, P.t1x, P.t1y, P.t1z);
+  const float qt2 = dot3(L.qx, L.qy, L.qz, P.t2x, P.t2y, P.t2z);
+  const float dt1 = dot3(fx, fy, fz, P.t1x, P.t1y, P.t1z);
+  const float dt2 = dot3(fx, fy, fz, P.t2x, P.t2y, P.t2z);
   P.den = den;
   float j0 = s0, j1 = s1;
   if (den != 0.0f) {
@@ -390,6 +363,55 @@ __device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, V
   const float ell = fmaxf(j1 - j0, 0.0f);
   P.alpha = 1.0f - __expf(-nrm.w * ell);
   return P;
+}
+
+// The rasteriser's piece: the cell's faces are read through the scalar cache,
+// two per step from one wave-uniform address, and the wave leaves the face loop
+// as soon as no lane's interval is left.
+template <typename VP, typename FP>
+__device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, VP faces, int nfaces, float4 nrm, FP tx,
+                                       float tau) {
+  const double D = (double)r * (double)r - L.qq;
+  if (D <= 0.0) {
+    Piece P;
+    P.alpha = 0.0f;
+    P.ux = P.uy = 0.0f;
+    P.bind0 = P.bind1 = -1;
+    P.s0 = 1.0f;
+    P.s1 = 0.0f;
+    return P;
+  }
+  const float sq = fsqrt((float)D);
+  Interval I = {-sq, sq, -1, -1};
+  const float nqx = -L.qx, nqy = -L.qy, nqz = -L.qz;
+  auto clip = [&](const float4 pl, float a, int f) {
+    clip_face(I, a, face_offset(pl, nqx, nqy, nqz) * frcp(a), true, f);
+  };
+  int f = 0;
+  bool more = nfaces >= 2;
+  float4 c0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), c1 = c0;
+  if (more) {
+    c0 = load4(faces);
+    c1 = load4(faces + 1);
+  }
+  while (more) {
+    const float4 p0 = c0, p1 = c1;
+    const int fn = f + 2;
+    if (fn + 2 <= nfaces) {   // the next pair is loaded while this one is tested
+      const VP fp = faces + __builtin_amdgcn_readfirstlane(fn);
+      c0 = load4(fp);
+      c1 = load4(fp + 1);
+    }
+    clip(p0, face_slope(R, p0), f);
+    clip(p1, face_slope(R, p1), f + 1);
+    f = fn;
+    more = f + 2 <= nfaces && __any(I.s0 < I.s1);
+  }
+  if (f + 1 == nfaces) {   // (its slope rounded as the other products here, not as face_slope)
+    const float4 pl = load4(faces + __builtin_amdgcn_readfirstlane(f));
+    clip(pl, dot3(R.fx, R.fy, R.fz, pl.x, pl.y, pl.z) + 0.0f, f);
+  }
+  return piece_dense<true>(R, L, I, nrm, tx, tau);
 }
 
 // A cell's Spherical-Voronoi axes and colours spread over the wave as the A
@@ -490,11 +512,11 @@ __device__ inline void radiance_wave(const float* __restrict__ tex, FP tx, FP rg
       for (int j = 1; j < KD; ++j) wk = (k == j) ? w[j] : wk;
       const FP t = tx + k * TEXW;
       float mx = -INFINITY;
-      for (int m = 0; m < MA; ++m) mx = fmaxf(mx, t[3 + 3 * m] * gx + t[4 + 3 * m] * gy + t[5 + 3 * m] * gz);
+      for (int m = 0; m < MA; ++m) mx = fmaxf(mx, dot3(t[3 + 3 * m], t[4 + 3 * m], t[5 + 3 * m], gx, gy, gz));
       float sum = 0.0f, sr = 0.0f, sg = 0.0f, sb = 0.0f;
       for (int m = 0; m < MA; ++m) {
         const float e =
-            __builtin_amdgcn_exp2f(t[3 + 3 * m] * gx + t[4 + 3 * m] * gy + t[5 + 3 * m] * gz - mx);
+            __builtin_amdgcn_exp2f(dot3(t[3 + 3 * m], t[4 + 3 * m], t[5 + 3 * m], gx, gy, gz) - mx);
         sum += e;
         sr += e * t[3 + 3 * MA + 3 * m];
         sg += e * t[4 + 3 * MA + 3 * m];
@@ -508,9 +530,10 @@ __device__ inline void radiance_wave(const float* __restrict__ tex, FP tx, FP rg
   }
 }
 
-// The same for the walk (a cell per lane, the texture read per lane): every softmax shifted by its largest logit, which keeps fewer values live
-// than the unshifted form with its rare shifted pass (the walk is held to 80
-// VGPRs).
+// The same with a cell per lane, the texture read per lane (the walk, where few
+// rays of the wave share a cell): every softmax shifted by its largest logit,
+// which keeps fewer values live than the unshifted form with its rare shifted
+// pass.
 __device__ inline void radiance_lane(const float* __restrict__ tx, const float* __restrict__ rgb, float ux, float uy,
                                      float fx, float fy, float fz, float tau, float& cr, float& cg, float& cb) {
   float w[KD];
