@@ -21,17 +21,17 @@
 //                 dipole split with displacement, radiance) and applies the
 //                 chain rule by hand, in reverse order of the forward; the
 //                 per-record sums (cell parameters, detail-site positions and
-//                 displacements) are reduced over the wave four at a time
-//                 (permlane32 / permlane16 swaps, then DPP, then an LDS
-//                 atomic add).  The next batch's records are loaded while a
-//                 batch is processed.
-//                 The 6 Spherical-Voronoi gradients of each (detail site k,
-//                 axis m) accumulate in registers over the chunk: the two
-//                 3-term dot products per (record, (k, m)) come from 32x32x2
-//                 FP32 MFMAs (records x site-axis pairs), the exponentials
-//                 and sums from the VALU, reading each record's direction,
-//                 dL/dc and per-site softmax terms from LDS.  Neighbour
-//                 gradients through binding faces gather per face in LDS.
+//                 displacements) are kept per lane in LDS and reduced once.
+//                 The next batch's records are loaded while a batch is
+//                 processed.
+//                 The sites' lobes come from 4x4x1 FP32 MFMAs (a record per
+//                 lane).  The 6 Spherical-Voronoi gradients of each (detail
+//                 site k, axis m) accumulate over the chunk: the two 3-term dot
+//                 products per (record, (k, m)) come from 32x32x2 FP32 MFMAs
+//                 (records x site-axis pairs), the exponentials from the VALU,
+//                 the sums over the records from 4x4x1 MFMAs.  Neighbour
+//                 gradients through binding faces are reduced over the wave
+//                 face by face and gather in LDS.
 //                 Everything is flushed with one global atomic per (chunk,
 //                 parameter).
 #include "pf_backward.hpp"
@@ -45,11 +45,11 @@ namespace {
 
 constexpr int BWD_THREADS = 64;     // one wave per workgroup
 constexpr int CHUNK = 2048;         // records per workgroup
-constexpr int FMAX_B = 128;         // faces gathered in LDS; faces beyond add to global directly
+constexpr int FMAX_B = 64;          // faces held in LDS (planes and sums); faces beyond go to global memory directly
+constexpr int CAM_B = 8;            // cameras held in LDS (with more, every record reads its own from global memory)
 constexpr int NCELL = 12;           // p(3) w r n(3) lambda rgb(3)
 constexpr int NSUM = NCELL + 3 * KD;  // + detail-site s(2), d per site
-constexpr int ISTAT = NSUM;           // + the cell's contribution sum (statistic)
-constexpr int KPAD = 65;            // row pitch of the per-site LDS table (bank spread)
+constexpr int CPAD = 68;             // row pitch of the transposed phase's LDS tables: 16-byte rows, banks spread
 
 // One workgroup per 16x16 tile of a view, one wave per 8x8 quadrant, lanes
 // row-major in the quadrant: the pixel layout of the store-mode raster, so
@@ -264,54 +264,63 @@ __global__ void k_chunk_fill(const uint32_t* __restrict__ cnt, const uint32_t* _
   }
 }
 
-// Sum of x over the wave, valid in lane 63: DPP butterflies within rows of
-// 16 lanes, then the row broadcasts of lane 15 and lane 31.
-__device__ inline float wave_total(float x) {
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xf, 0xf, false));  // quad [1,0,3,2]
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xf, 0xf, false));  // quad [2,3,0,1]
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false)); // row half mirror
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x140, 0xf, 0xf, false)); // row mirror
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x142, 0xa, 0xf, false)); // row bcast 15
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x143, 0xc, 0xf, false)); // row bcast 31
-  return x;
+// The chunk's per-record sums are kept per lane in LDS, four values in a float4,
+// and reduced over the lanes once at the end of the chunk.  A lane updates its own
+// slots by a plain read, add and write, the read issued ahead of the arithmetic
+// that gives the values.  (Reduced over the wave in every batch, four values at a
+// time with permlane swaps and DPP adds, they took sixteen instructions and a
+// dozen waits per four values; by LDS float atomics of all 64 lanes, which the
+// LDS takes about one lane at a time, k_bwd_cell took 101 instead of 37 ms.)
+constexpr int ACC_XY = NCELL / 4;           // rows of the sites' s: two sites each
+constexpr int ACC_D = ACC_XY + KD / 2;      // rows of the sites' d: four sites each
+constexpr int ACC_ROWS = ACC_D + KD / 4;
+static_assert(NCELL % 4 == 0 && KD % 4 == 0, "the sums go four to a row");
+typedef float4 AccRow[64];
+
+// facc[f] += (x, y, z, w) for the lanes with f >= 0, face by face: a chunk's
+// records are neighbouring pixels of one cell, so a wave holds few faces, and
+// LDS atomics, which the LDS takes about one lane at a time, cost more than a
+// reduction per face (4.5 of k_bwd_cell's 36 ms).  In the reduction permlane32
+// swaps pair x with y and z with w, a permlane16 swap pairs the results, so that
+// after two adds rows 0..3 of the wave hold partial sums of x, z, y, w; four DPP
+// steps finish the row sums.  All lanes take part.
+__device__ inline void face_sums(float (*facc)[4], int f, float x, float y, float z, float w) {
+  const int lane = threadIdx.x;
+  const int comp = ((lane >> 4) & 1) * 2 + (lane >> 5);
+  for (uint64_t m = __ballot(f >= 0); m;) {
+    const int g = __builtin_amdgcn_readlane(f, __ffsll((long long)m) - 1);
+    const bool on = f == g;
+    m &= ~__ballot(on);
+    const float x0 = on ? x : 0.0f, y0 = on ? y : 0.0f, z0 = on ? z : 0.0f, w0 = on ? w : 0.0f;
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(y0), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(z0), __float_as_uint(w0), false, false);
+    const float s01 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const float s23 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
+    float t = __uint_as_float(c[0]) + __uint_as_float(c[1]);
+    t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0xB1, 0xf, 0xf, false));  // quad [1,0,3,2]
+    t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x4E, 0xf, 0xf, false));  // quad [2,3,0,1]
+    t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x141, 0xf, 0xf, false)); // row half mirror
+    t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x140, 0xf, 0xf, false)); // row mirror
+    if ((lane & 15) == 0) atomicAdd(&facc[g][comp], t);
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
-// acc[i] += sum over the wave of (valid ? v : 0); acc is the wave's own LDS.
-// The update is an LDS atomic add without return, so that the wave does not
-// wait for a read of acc[i] (a read-add-write waited for each of them: 50.7
-// instead of 45.0 ms for the kernel).
-__device__ inline void sum_to(float* acc, int i, bool valid, float v) {
-  const float t = wave_total(valid ? v : 0.0f);
-  if ((threadIdx.x & 63) == 63) atomicAdd(&acc[i], t);
+// row[lane] = o + (v0, v1, v2, v3); o was read from there before.
+__device__ inline void acc_add(AccRow& row, float4 o, bool valid, float v0, float v1, float v2, float v3) {
+  o.x += v0;
+  o.y += v1;
+  o.z += v2;
+  o.w += v3;
+  if (valid) row[threadIdx.x] = o;
 }
 
-
-// Four wave sums at once: acc[dst] += sum over the wave of (valid ? v_j : 0)
-// for j = sum4_value(lane), in the first lane of each row of 16.  permlane32
-// swaps pair v0 with v1 and v2 with v3, a permlane16 swap pairs the results,
-// so that after two adds rows 0..3 of the wave hold partial sums of v0, v2,
-// v1, v3; four DPP steps finish the row sums, and the first lane of each row
-// adds its value to acc[dst] (LDS atomic).  dst is computed by the caller from
-// sum4_value(lane), a per-lane constant, so that the choice of the
-// destination costs no branch.
-__device__ inline int sum4_value(int lane) { return ((lane >> 4) & 1) * 2 + (lane >> 5); }
-
-__device__ inline void sum4_to(float* acc, int dst, bool valid, float v0, float v1, float v2, float v3) {
-  v0 = valid ? v0 : 0.0f;
-  v1 = valid ? v1 : 0.0f;
-  v2 = valid ? v2 : 0.0f;
-  v3 = valid ? v3 : 0.0f;
-  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v2), __float_as_uint(v3), false, false);
-  const float s01 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const float s23 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
-  const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
-  float t = __uint_as_float(c[0]) + __uint_as_float(c[1]);
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0xB1, 0xf, 0xf, false));  // quad [1,0,3,2]
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x4E, 0xf, 0xf, false));  // quad [2,3,0,1]
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x141, 0xf, 0xf, false)); // row half mirror
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x140, 0xf, 0xf, false)); // row mirror
-  if ((threadIdx.x & 15) == 0) atomicAdd(&acc[dst], t);
+// Where sum t (< NSUM) stands: row and component.
+__device__ inline int2 acc_slot(int t) {
+  if (t < NCELL) return make_int2(t >> 2, t & 3);
+  const int k = (t - NCELL) / 3, c = (t - NCELL) % 3;
+  return c < 2 ? make_int2(ACC_XY + (k >> 1), 2 * (k & 1) + c) : make_int2(ACC_D + (k >> 2), k & 3);
 }
 
 __device__ inline float softplus_b(float x) { return x > 20.0f ? x : log1pf(expf(x)); }
@@ -357,67 +366,79 @@ __device__ inline void len_rlen(double x2, double& len, double& rlen) {
 // (in float64 the kernel took 6% longer; against the oracle adjoint the
 // worst per-component error over the GPU gradient tests rose from 7e-6 to
 // 1.6e-4, on the normal of one small scene, the others unchanged).
-__device__ inline void sv_backward(const float* __restrict__ tx, double ux_d, double uy_d, const double* ge,
-                                   double& gux, double& guy, float* acc, bool valid) {
+__device__ inline void sv_backward(const float* site, const float* off, double ux_d, double uy_d, const double* ge,
+                                   double& gux, double& guy, AccRow* acc, bool valid) {
   const float ux = (float)ux_d, uy = (float)uy_d;
   const float u2 = ux * ux + uy * uy;
   const float iun = u2 > 0.0f ? __builtin_amdgcn_rsqf(u2) : 0.0f;
   const float un = u2 * iun;
-  const int j4 = sum4_value(threadIdx.x);   // site k0 + j4 / 2, coordinate j4 % 2
-  static_assert(KD % 2 == 0, "the site sums go two sites at a time");
+  const int lane = threadIdx.x;
 #pragma unroll
   for (int k0 = 0; k0 < KD; k0 += 2) {
+    float4 o = acc[ACC_XY + k0 / 2][lane];
     float vx[2], vy[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = k0 + h;
-      const float sx = tx[k * TEXW], sy = tx[k * TEXW + 1];
+      const float sx = site[3 * k], sy = site[3 * k + 1];
       const float ex = ux - sx, ey = uy - sy;
       const float d2 = ex * ex + ey * ey;
-      const float rd = d2 > 0.0f ? __builtin_amdgcn_rsqf(d2) : 0.0f;
+      const float rq = __builtin_amdgcn_rsqf(d2);
+      const float rd = d2 > 0.0f ? rq : 0.0f;
       const float dist = d2 * rd;
-      float lx, ly;
-      if (un > 0.0f && dist > 0.0f) {
-        const float e = (sx * sx + sy * sy - 2.0f * (ux * sx + uy * sy)) * frcp(dist + un);   // |u - s| - |u|
-        const float f = rd * iun;
-        lx = (-ux * e - sx * un) * f;
-        ly = (-uy * e - sy * un) * f;
-      } else {
-        lx = ex * rd;
-        ly = ey * rd;
-      }
+      // both forms, and a choice without a branch; |u - s| - |u| as in the weights
+      const float e = off[k];
+      const float f = rd * iun;
+      const float ax = (-ux * e - sx * un) * f, ay = (-uy * e - sy * un) * f;
+      const bool both = un > 0.0f && dist > 0.0f;
+      const float lx = both ? ax : ex * rd, ly = both ? ay : ey * rd;
       gux += ge[k] * (double)lx;
       guy += ge[k] * (double)ly;
       const float gk = (float)ge[k];
       vx[h] = -gk * ex * rd;
       vy[h] = -gk * ey * rd;
     }
-    sum4_to(acc, NCELL + 3 * k0 + j4 + (j4 >> 1), valid, vx[0], vy[0], vx[1], vy[1]);
+    acc_add(acc[ACC_XY + k0 / 2], o, valid, vx[0], vy[0], vx[1], vy[1]);
   }
 }
 
 // Two waves per SIMD: at most 256 VGPRs, which the per-record float64
 // chain fills without spilling (at three waves, 168 VGPRs, it spilled and ran
-// 5% slower).
+// 5% slower), and eight workgroups' LDS per CU.
+// The kernel is bound by the vector instructions it issues (77% of the SIMDs'
+// cycles) and, with two waves to hide them, by the waits between.  37.1 ms for
+// the 8 views of 1600x1066 of a training step at 1,048,576 cells became 30.5:
+// the sites' lobes and the transposed sums as 4x4x1 FP32 MFMAs, the shifts and
+// dL/dw as initial values of the transposed MFMAs, sums kept per lane, choices
+// instead of branches (together 37.1 -> 36.4, the waits having become the bound);
+// then planes, cameras, axes and colours in LDS, the face sums without LDS atomics
+// and 16-byte LDS reads (-> 32.3), the sites' distances shared by weights and
+// derivatives and a pixel's row without an integer division (-> 30.5).
 __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) k_bwd_cell(
-    const pf_camera* __restrict__ cams, const int4* __restrict__ ri, const float4* __restrict__ rf,
+    const pf_camera* __restrict__ cams, int ncam, const int4* __restrict__ ri, const float4* __restrict__ rf,
     const int32_t* __restrict__ order, const int4* __restrict__ chunks, const float* __restrict__ prm_p,
     const float* __restrict__ radius, const float* __restrict__ normal, const float* __restrict__ lamv,
     const float* __restrict__ tex, const int32_t* __restrict__ row, const int32_t* __restrict__ nrast,
     const int32_t* __restrict__ col, const float4* __restrict__ plane, float sigma_scale, float tau_, pf_grads G,
     const float* __restrict__ rta, float lambda_n, float* __restrict__ contribution) {
-  __shared__ float4 st_dir[64];          // per record: ray direction (float), 0
-  __shared__ float4 st_gc[64];           // per record: dL/dc, 0
-  __shared__ float2 st_k[KD][KPAD];      // per record and site: softmax shift, dL/dw_k
-  __shared__ float acc[NSUM + 1];
-  __shared__ float4 facc[FMAX_B];
+  __shared__ __align__(16) float st_dir[4][CPAD];   // by component (the fourth 0) and record: ray direction
+  __shared__ __align__(16) float st_gc[4][CPAD];    // the same of dL/dc
+  __shared__ __align__(16) float st_sh[KD][CPAD];   // by site and record: minus the softmax shift
+  __shared__ __align__(16) float st_gw[KD][CPAD];   // the same of minus dL/dw_k
+  __shared__ AccRow acc[ACC_ROWS];       // per-lane sums over the chunk's batches
+  float ta_sum = 0.0f;                   // the same of the contribution
+  __shared__ float facc[FMAX_B][4];      // per face: dL/dm, dL/dw_j
+  __shared__ float4 s_pl[FMAX_B];        // the cell's raster faces
+  __shared__ pf_camera s_cam[CAM_B];
+  __shared__ double s_iw[CAM_B];         // 1 / width
   __shared__ double s_fr[12];            // the cell's face frame (wave-uniform)
   // zeros, read back as a per-batch offset that the compiler cannot see
   // through: values derived from it are recomputed in every batch instead of
   // being hoisted out of the record loop and held (an LDS load, unlike an
   // empty asm statement, is no memory write, so the texture reads stay
   // scalar loads)
-  __shared__ int s_zero[64];
+  __shared__ int s_zero[2];
+  __shared__ float s_tex[KD * TEXW];     // the cell's texture
 
   const int4 ch = chunks[blockIdx.x];
   const int ci = ch.x;
@@ -426,9 +447,28 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
   const int nf = nrast[ci];
   const int nfl = min(nf, FMAX_B);
   const float* __restrict__ txc = tex + (int64_t)ci * KD * TEXW;
-  for (int t = lane; t < NSUM + 1; t += BWD_THREADS) acc[t] = 0.0f;
-  s_zero[lane] = 0;
-  for (int t = lane; t < nfl; t += BWD_THREADS) facc[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int t = 0; t < ACC_ROWS; ++t) acc[t][lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (lane < 2) s_zero[lane] = 0;
+  st_dir[3][lane] = st_gc[3][lane] = 0.0f;
+  for (int t = lane; t < KD * TEXW; t += BWD_THREADS) s_tex[t] = txc[t];
+  // the sites' (s, d), wave-uniform: scalar registers
+  float site0[3 * KD];
+#pragma unroll
+  for (int k = 0; k < KD; ++k) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) site0[3 * k + c] = txc[k * TEXW + c];
+  }
+  static_assert(FMAX_B <= BWD_THREADS, "a face per lane");
+  if (lane < nfl) {
+    s_pl[lane] = plane[r0 + lane];
+    for (int c = 0; c < 4; ++c) facc[lane][c] = 0.0f;
+  }
+  if (ncam <= CAM_B) {
+    if (lane < ncam) s_iw[lane] = 1.0 / (double)cams[lane].width;
+    static_assert(sizeof(pf_camera) % 4 == 0, "copied by words");
+    for (int t = lane; t < ncam * (int)(sizeof(pf_camera) / 4); t += BWD_THREADS)
+      reinterpret_cast<uint32_t*>(s_cam)[t] = reinterpret_cast<const uint32_t*>(cams)[t];
+  }
 
   // cell constants, computed exactly as the build's per-cell record
   const float px = prm_p[3 * ci], py = prm_p[3 * ci + 1], pz = prm_p[3 * ci + 2];
@@ -455,9 +495,6 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
   }
   __syncthreads();
 
-  // (site, axis) pair of this lane when the transposed phase's sums are
-  // flushed
-  const int km = lane >> 3, mm = lane & 7;
   // The transposed phase takes its two 3-term dot products per (record,
   // site-axis pair) from 32x32x2 FP32 MFMAs: logits L[r][km] = d_r . a_km
   // (axes scaled by log2(e)) and G[r][km] = gC_r . c_km, each as two MFMAs
@@ -466,21 +503,11 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
   // + v % 4 of register v, so a lane accumulates two site-axis pairs (cb = 0,
   // 1) over its half of the records, and the halves are added at the end.
   const int hh = lane >> 5, j32 = lane & 31;
-  float Ba[2][2], Bc[2][2];   // B operands [cb][step]: component 2 step + hh of a_km (scaled) and c_km
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    const int kmx = 32 * cb + j32;
-    const float* t = txc + (kmx >> 3) * TEXW;
-    const int m = kmx & 7;
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      const int comp = 2 * st + hh;
-      Ba[cb][st] = comp < 3 ? t[3 + 3 * m + comp] * LOG2E_F : 0.0f;
-      Bc[cb][st] = comp < 3 ? t[3 + 3 * MA + 3 * m + comp] : 0.0f;
-    }
-  }
-  float sa[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // dL/da partial sums [cb][xyz]
-  float sc[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // dL/dc partial sums [cb][rgb]
+  // dL/da and dL/dc partial sums of each half of the columns, as the results of
+  // 4x4x1 MFMAs (sixteen blocks; block b of half cb: km = 32 cb + 4 (b % 8) + i in
+  // register i, component j in lane 4 b + j, lanes 32 and up the other records)
+  vec4f sa[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+  vec4f sc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 
   // the records of the next batch are loaded while this one is processed:
   // its order entries at the start of a batch, the records themselves once
@@ -495,10 +522,21 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     n_ta = rta[ridx];
   }
   for (int base = ch.y; base < ch.z; base += 64) {
-    // the texture is re-read per record batch (scalar loads, offset by the
-    // opaque zero) rather than held in registers across the loop
-    const int zo = s_zero[(base >> 6) & 63];   // 0
-    const float* __restrict__ tx = txc + __builtin_amdgcn_readfirstlane(zo);
+    // the axes and colours are re-read per record batch (offset by the opaque
+    // zero) rather than held in registers across the loop
+    const int zo = s_zero[(base >> 6) & 1];   // 0
+    // (copies that the compiler cannot see through, so that what is derived from
+    // them is neither hoisted out of the loop nor kept from one use to the next,
+    // and spilled)
+    float site[3 * KD];
+    auto renew = [&]() {
+#pragma unroll
+      for (int i = 0; i < 3 * KD; ++i) {
+        site[i] = site0[i];
+        asm volatile("" : "+s"(site[i]));
+      }
+    };
+    renew();
     const int idx = base + lane;
     const bool valid = idx < ch.z;
     const int nvalid = min(64, ch.z - base);
@@ -510,19 +548,33 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     const int n_ridx = order[min(nidx, ch.z - 1)];   // (in the chunk; used only if n_valid)
     const int view = rec_view(rec.w);
     const int b0 = rec_bind0(rec.w), b1 = rec_bind1(rec.w);
-    // the binding faces' planes, loaded before the ray set-up
-    const float4 pl0 = (b0 >= 0 && b0 < nf) ? plane[r0 + b0] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    const float4 pl1 = (b1 >= 0 && b1 < nf) ? plane[r0 + b1] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    // the camera is copied at once (its loads issued together) rather than
-    // read field by field behind the branches of the ray set-up
-    const pf_camera cam = cams[valid ? view : 0];
-    const int pxl = rec.y % cam.width, pyl = rec.y / cam.width;
+    // the binding faces' planes and the camera, from LDS where they fit
+    const bool on0 = b0 >= 0 && b0 < nf, on1 = b1 >= 0 && b1 < nf;
+    float4 pl0 = s_pl[min(max(b0, 0), FMAX_B - 1)], pl1 = s_pl[min(max(b1, 0), FMAX_B - 1)];
+    if (nf > FMAX_B) {
+      if (on0 && b0 >= FMAX_B) pl0 = plane[r0 + b0];
+      if (on1 && b1 >= FMAX_B) pl1 = plane[r0 + b1];
+    }
+    pl0 = on0 ? pl0 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    pl1 = on1 ? pl1 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int vi = valid ? view : 0;
+    pf_camera cam;
+    if (ncam <= CAM_B) cam = s_cam[vi];
+    else cam = cams[vi];
+    // row and column of the pixel: (pix + 1/2) / width is no nearer than 1 / (2
+    // width) to a whole number, far more than float64's rounding
+    const double iw = ncam <= CAM_B ? s_iw[vi] : 1.0 / (double)cam.width;
+    const int pyl = (int)(((double)rec.y + 0.5) * iw), pxl = rec.y - pyl * cam.width;
     const RayD R = make_ray(cam, pxl + 0.5, pyl + 0.5);
     const float fx = R.fx, fy = R.fy, fz = R.fz;
     const float g_alpha = gf.x;
     const float gcr = gf.y, gcg = gf.z, gcb = gf.w;
-    st_dir[lane] = make_float4(fx, fy, fz, 0.0f);
-    st_gc[lane] = make_float4(gcr, gcg, gcb, 0.0f);
+    st_dir[0][lane] = fx;
+    st_dir[1][lane] = fy;
+    st_dir[2][lane] = fz;
+    st_gc[0][lane] = gcr;
+    st_gc[1][lane] = gcg;
+    st_gc[2][lane] = gcb;
 
     // ---------------- forward recompute.  Interval ends in float32 as in
     // piece_geometry; the face frame, displacement and texture point in
@@ -564,35 +616,26 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     const double dt1 = ddx * d1x + ddy * d1y + ddz * d1z;
     const double dt2 = ddx * d2x + ddy * d2y + ddz * d2z;
     const bool nzden = den != 0.0;
-    double idn = 0.0, sbar = 0.0, sxx = 0.0, delta = 0.0;
+    // a ray parallel to the face (den = 0) has no displaced face: with 1/den
+    // set to 0 every gradient through it is 0, and nothing has to branch
+    const double rden = rcp_d(den);
+    const double idn = nzden ? rden : 0.0, sbar = -qn * idn;
+    const double ubx = qt1 + sbar * dt1, uby = qt2 + sbar * dt2;
+    double delta = 0.0;
     float wd[KD];   // displacement weights at ubar
-    double ubx = 0.0, uby = 0.0;
-    double j0 = s0, j1 = s1;
-    int sel0 = 0, sel1 = 0;   // 1: the end is the displaced face
-    double ux, uy, S;
-    if (nzden) {
-      idn = rcp_d(den);
-      sbar = -qn * idn;
-      ubx = qt1 + sbar * dt1;
-      uby = qt2 + sbar * dt2;
-      sv_weights(tx, (float)ubx, (float)uby, tau, wd);
+    float od[KD], our[KD];   // the sites' |u - s_k| - |u|
+    sv_weights<3>(site, (float)ubx, (float)uby, tau, wd, od);
 #pragma unroll
-      for (int k = 0; k < KD; ++k) delta += (double)wd[k] * (double)tx[k * TEXW + 2];
-      sxx = (delta - qn) * idn;
-      if (den > 0.0) {
-        sel1 = sxx < (double)s1;
-        j1 = sel1 ? sxx : (double)s1;
-      } else {
-        sel0 = sxx > (double)s0;
-        j0 = sel0 ? sxx : (double)s0;
-      }
-      S = sxx;
-    } else {
-#pragma unroll
-      for (int k = 0; k < KD; ++k) wd[k] = 0.0f;
-      S = 0.5 * ((double)s0 + (double)s1);
-      if (!(qn < 0.0)) j1 = j0;
-    }
+    for (int k = 0; k < KD; ++k) delta += (double)wd[k] * (double)site[3 * k + 2];
+    const double sxx = (delta - qn) * idn;
+    // whether an end is the displaced face
+    const bool sel1 = nzden && den > 0.0 && sxx < (double)s1;
+    const bool sel0 = nzden && !(den > 0.0) && sxx > (double)s0;
+    const double j0 = sel0 ? sxx : (double)s0;
+    double j1 = sel1 ? sxx : (double)s1;
+    j1 = !nzden && !(qn < 0.0) ? j0 : j1;
+    const double S = nzden ? sxx : 0.5 * ((double)s0 + (double)s1);
+    double ux, uy;
     ux = qt1 + S * dt1;
     uy = qt2 + S * dt2;
     const float ell = (float)fmax(j1 - j0, 0.0);
@@ -613,27 +656,62 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     // ---------------- radiance: weights at u, the sites' Spherical-Voronoi
     // colours sv_k(d) and the softmax backward of the weights
     float wr[KD];
-    sv_weights(tx, (float)ux, (float)uy, tau, wr);
+    renew();
+    sv_weights<3>(site, (float)ux, (float)uy, tau, wr, our);
     double sum_wg = 0.0;
     float gwr[KD];
     const float gx = fx * LOG2E_F, gy = fy * LOG2E_F, gz = fz * LOG2E_F;
+    bool in_range = true;
+    const WaveTex W = wave_tex(s_tex + zo);
+    // w_k softmax_m(a_km.d) = 2^(a_km.d log2(e) - shift_k), shift_k = sh - log2(w_k / sum)
+    // (sh = 0 for the unshifted sums)
+    auto lobes = [&](int k, const vec4f s) {
+      in_range = in_range && s[3] >= 0x1p-100f && s[3] <= 0x1p100f;
+      const float inv = frcp(s[3]);
+      gwr[k] = (gcr * s[0] + gcg * s[1] + gcb * s[2]) * inv;   // dL/dw_k = gC . sv_k
+      const float wi = wr[k] * inv, lw = __log2f(wi);
+      st_sh[k][lane] = valid && wi > 0.0f ? lw : -INFINITY;
+      st_gw[k][lane] = -gwr[k];
+    };
+    lobes(0, wave_lobes<0>(W, gx, gy, gz));
+    lobes(1, wave_lobes<1>(W, gx, gy, gz));
+    __builtin_amdgcn_sched_barrier(0);
+    lobes(2, wave_lobes<2>(W, gx, gy, gz));
+    lobes(3, wave_lobes<3>(W, gx, gy, gz));
+    __builtin_amdgcn_sched_barrier(0);
+    lobes(4, wave_lobes<4>(W, gx, gy, gz));
+    lobes(5, wave_lobes<5>(W, gx, gy, gz));
+    __builtin_amdgcn_sched_barrier(0);
+    lobes(6, wave_lobes<6>(W, gx, gy, gz));
+    lobes(7, wave_lobes<7>(W, gx, gy, gz));
+    __builtin_amdgcn_sched_barrier(0);
+    if (!in_range) {
+      // a site's sum left float32's range: again with shifted logits
+#pragma unroll 1
+      for (int k = 0; k < KD; ++k) {
+        float wk = wr[0];
 #pragma unroll
-    for (int k = 0; k < KD; ++k) {
-      float sum, sr, sg, sb;
-      const float sh = sv_lobes(tx + k * TEXW, gx, gy, gz, sum, sr, sg, sb);
-      const float inv = frcp(sum);
-      gwr[k] = (gcr * sr + gcg * sg + gcb * sb) * inv;   // dL/dw_k = gC . sv_k
-      sum_wg += (double)wr[k] * (double)gwr[k];
-      // w_k softmax_m(a_km.d) = 2^(a_km.d log2(e) - shift_k), shift_k = sh - log2(w_k / sum)
-      const float wi = wr[k] * inv;
-      st_k[k][lane] = make_float2(valid && wi > 0.0f ? sh - __log2f(wi) : INFINITY, gwr[k]);
+        for (int j = 1; j < KD; ++j) wk = (k == j) ? wr[j] : wk;
+        float sum, sr, sg, sb;
+        const float sh = sv_lobes(txc + k * TEXW, gx, gy, gz, sum, sr, sg, sb);
+        const float inv = frcp(sum);
+        const float gk = (gcr * sr + gcg * sg + gcb * sb) * inv;
+        const float wi = wk * inv;
+        st_sh[k][lane] = valid && wi > 0.0f ? __log2f(wi) - sh : -INFINITY;
+        st_gw[k][lane] = -gk;
+#pragma unroll
+        for (int j = 0; j < KD; ++j) gwr[j] = (k == j) ? gk : gwr[j];
+      }
     }
+#pragma unroll
+    for (int k = 0; k < KD; ++k) sum_wg += (double)wr[k] * (double)gwr[k];
     double gux = 0.0, guy = 0.0;
     {
       double ge[KD];
 #pragma unroll
       for (int k = 0; k < KD; ++k) ge[k] = -(double)tau * (double)wr[k] * ((double)gwr[k] - sum_wg);
-      sv_backward(tx, ux, uy, ge, gux, guy, acc, valid);
+      renew();
+      sv_backward(site, our, ux, uy, ge, gux, guy, acc, valid);
     }
     // u = (qt1 + S dt1, qt2 + S dt2)
     double g_qt1 = gux, g_qt2 = guy, g_dt1 = gux * S, g_dt2 = guy * S;
@@ -642,31 +720,27 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     else { g_s0 += (float)(0.5 * g_S); g_s1 += (float)(0.5 * g_S); }
 
     // ---------------- displaced face sx = (delta - qn)/den
-    double g_qn = 0.0, g_den = 0.0;
-    if (nzden) {
-      const double g_delta = g_sx * idn;
-      g_qn -= g_sx * idn;
-      g_den -= g_sx * sxx * idn;
-      double sum_w = 0.0;
-      double gw[KD];
-      static_assert(KD % 4 == 0 && NCELL % 4 == 0, "these wave sums go four at a time");
+    const double g_delta = g_sx * idn;
+    double g_qn = -(g_sx * idn), g_den = -(g_sx * sxx * idn);
+    double sum_w = 0.0;
+    double gw[KD];
 #pragma unroll
-      for (int k = 0; k < KD; k += 4)
-        sum4_to(acc, NCELL + 3 * (k + sum4_value(lane)) + 2, valid,
-                (float)(g_delta * (double)wd[k]), (float)(g_delta * (double)wd[k + 1]),
-                (float)(g_delta * (double)wd[k + 2]), (float)(g_delta * (double)wd[k + 3]));
+    for (int k = 0; k < KD; k += 4)
+      acc_add(acc[ACC_D + k / 4], acc[ACC_D + k / 4][lane], valid, (float)(g_delta * (double)wd[k]),
+              (float)(g_delta * (double)wd[k + 1]), (float)(g_delta * (double)wd[k + 2]),
+              (float)(g_delta * (double)wd[k + 3]));
 #pragma unroll
-      for (int k = 0; k < KD; ++k) {
-        gw[k] = g_delta * (double)tx[k * TEXW + 2];
-        sum_w += (double)wd[k] * gw[k];
-      }
+    for (int k = 0; k < KD; ++k) {
+      gw[k] = g_delta * (double)site[3 * k + 2];
+      sum_w += (double)wd[k] * gw[k];
+    }
+    {
       double gubx = 0.0, guby = 0.0;
-      {
-        double ge[KD];
+      double ge[KD];
 #pragma unroll
-        for (int k = 0; k < KD; ++k) ge[k] = -(double)tau * (double)wd[k] * (gw[k] - sum_w);
-        sv_backward(tx, ubx, uby, ge, gubx, guby, acc, valid);
-      }
+      for (int k = 0; k < KD; ++k) ge[k] = -(double)tau * (double)wd[k] * (gw[k] - sum_w);
+      renew();
+      sv_backward(site, od, ubx, uby, ge, gubx, guby, acc, valid);
       // ubar = (qt1 + sbar dt1, qt2 + sbar dt2), sbar = -qn/den
       g_qt1 += gubx;
       g_qt2 += guby;
@@ -678,7 +752,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     }
 
     // ---------------- frame: q.nhat, d.nhat, q.t1, d.t1, q.t2, d.t2 (float64)
-    fo = s_zero[(base >> 6) & 63];
+    fo = s_zero[(base >> 6) & 1];
     dnx = s_fr[fo]; dny = s_fr[fo + 1]; dnz = s_fr[fo + 2];
     d1x = s_fr[fo + 3]; d1y = s_fr[fo + 4]; d1z = s_fr[fo + 5];
     d2x = s_fr[fo + 6]; d2y = s_fr[fo + 7]; d2z = s_fr[fo + 8];
@@ -714,8 +788,14 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     // ---------------- ends of the bounded interval
     float g_beta = 0.0f, g_r = 0.0f, g_wi = 0.0f;
     float gpx = 0.0f, gpy = 0.0f, gpz = 0.0f;   // explicit p_i terms (planes)
+    // (returns what the binding face's plane gets, for the sums in LDS; face -1: none)
+    struct FaceGrad {
+      int f;
+      float x, y, z, w;
+    };
     auto end_grad = [&](int b, const float4& pl, float s, float a, float ge, bool upper) {
-      if (ge == 0.0f) return;
+      FaceGrad fg = {-1, 0.0f, 0.0f, 0.0f, 0.0f};
+      if (ge == 0.0f) return fg;
       if (b == -1) {                       // s = +-sqrt(r^2 - |q|^2)
         const float inv = frcp(sq);
         const float sgn = upper ? 1.0f : -1.0f;
@@ -742,10 +822,11 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
         gpz -= gmz;
         g_wi += 0.5f * gh;
         if (b < FMAX_B) {
-          atomicAdd(&facc[b].x, gmx);
-          atomicAdd(&facc[b].y, gmy);
-          atomicAdd(&facc[b].z, gmz);
-          atomicAdd(&facc[b].w, -0.5f * gh);
+          fg.f = b;
+          fg.x = gmx;
+          fg.y = gmy;
+          fg.z = gmz;
+          fg.w = -0.5f * gh;
         } else {
           const int j = col[r0 + b];
           if (j >= 0) {
@@ -758,10 +839,13 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
           }
         }
       }
+      return fg;
     };
-    if (valid) {
-      end_grad(b0, pl0, s0, a0, g_s0, false);
-      end_grad(b1, pl1, s1, a1, g_s1, true);
+    {
+      const FaceGrad e0 = end_grad(b0, pl0, s0, a0, valid ? g_s0 : 0.0f, false);
+      face_sums(facc, e0.f, e0.x, e0.y, e0.z, e0.w);
+      const FaceGrad e1 = end_grad(b1, pl1, s1, a1, valid ? g_s1 : 0.0f, true);
+      face_sums(facc, e1.f, e1.x, e1.y, e1.z, e1.w);
     }
     // q = oc - beta d, beta = oc.d, oc = o - p_i
     const float gqd = gqx * fx + gqy * fy + gqz * fz;
@@ -769,15 +853,12 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     gpy += -(gqy - gqd * fy) - g_beta * fy;
     gpz += -(gqz - gqd * fz) - g_beta * fz;
 
-    // ---------------- per-record sums over the wave (lanes past the chunk
-    // add zero)
-    {
-      const float cellv[NCELL] = {gpx, gpy, gpz, g_wi, g_r, gnx, gny, gnz, g_lam, gcr, gcg, gcb};
-#pragma unroll
-      for (int i = 0; i < NCELL; i += 4)
-        sum4_to(acc, i + sum4_value(lane), valid, cellv[i], cellv[i + 1], cellv[i + 2], cellv[i + 3]);
-      if (contribution) sum_to(acc, ISTAT, valid, ta);
-    }
+    // ---------------- the record's own sums
+    acc_add(acc[0], acc[0][lane], valid, gpx, gpy, gpz, g_wi);
+    acc_add(acc[1], acc[1][lane], valid, g_r, gnx, gny, gnz);
+    acc_add(acc[2], acc[2][lane], valid, g_lam, gcr, gcg, gcb);
+    static_assert(NCELL == 12, "three rows: p and power, radius and normal, occ_logit and rgb");
+    ta_sum += valid ? ta : 0.0f;
 
     // ---------------- Spherical-Voronoi gradients over (record, site-axis
     // pair (k, m)):
@@ -785,46 +866,86 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     //   dL/da_km += w_k v (gC.c_km - gC.sv_k) d
     // with w_k v = 2^(a_km.d log2(e) - shift) (the per-record shift in st_k)
     __builtin_amdgcn_wave_barrier();
+    float Ba[2][2], Bc[2][2];   // B operands [cb][step]: component 2 step + hh of a_km (scaled) and c_km
+  #pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      const int kmx = 32 * cb + j32;
+      const float* t = s_tex + zo + (kmx >> 3) * TEXW;
+      const int m = kmx & 7;
+  #pragma unroll
+      for (int st = 0; st < 2; ++st) {
+        const int comp = 2 * st + hh;
+        Ba[cb][st] = comp < 3 ? t[3 + 3 * m + comp] * LOG2E_F : 0.0f;
+        Bc[cb][st] = comp < 3 ? t[3 + 3 * MA + 3 * m + comp] : 0.0f;
+      }
+    }
     // rows of records past the chunk hold direction, dL/dc = 0 and an
     // infinite shift, so they add exact zeros
     typedef float f16v __attribute__((ext_vector_type(16)));
-    const f16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const int ks0 = j32 >> 3, ks1 = (32 + j32) >> 3;   // sites of the lane's two columns
     for (int rb = 0; rb < 2 && 32 * rb < nvalid; ++rb) {
       // A operands: component 2 step + hh of record 32 rb + l % 32
-      const float4 da = st_dir[32 * rb + j32];
-      const float4 ga = st_gc[32 * rb + j32];
-      const float ad0 = hh ? da.y : da.x, ad1 = hh ? 0.0f : da.z;
-      const float ag0 = hh ? ga.y : ga.x, ag1 = hh ? 0.0f : ga.z;
-      f16v L0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad0, Ba[0][0], zero16, 0, 0, 0);
+      const int ra = 32 * rb + j32;
+      const float ad0 = st_dir[hh][ra], ad1 = st_dir[2 + hh][ra];
+      const float ag0 = st_gc[hh][ra], ag1 = st_gc[2 + hh][ra];
+      // the results start from minus the shift and minus dL/dw_k, so that they
+      // are the exponent a_km.d log2(e) - shift and gC.c_km - gC.sv_k
+      f16v L0, L1, G0, G1;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int r = 32 * rb + 8 * g + 4 * hh;
+        const float4 h0 = *reinterpret_cast<const float4*>(&st_sh[ks0][r]);
+        const float4 h1 = *reinterpret_cast<const float4*>(&st_sh[ks1][r]);
+        const float4 g0 = *reinterpret_cast<const float4*>(&st_gw[ks0][r]);
+        const float4 g1 = *reinterpret_cast<const float4*>(&st_gw[ks1][r]);
+        L0[4 * g] = h0.x; L0[4 * g + 1] = h0.y; L0[4 * g + 2] = h0.z; L0[4 * g + 3] = h0.w;
+        L1[4 * g] = h1.x; L1[4 * g + 1] = h1.y; L1[4 * g + 2] = h1.z; L1[4 * g + 3] = h1.w;
+        G0[4 * g] = g0.x; G0[4 * g + 1] = g0.y; G0[4 * g + 2] = g0.z; G0[4 * g + 3] = g0.w;
+        G1[4 * g] = g1.x; G1[4 * g + 1] = g1.y; G1[4 * g + 2] = g1.z; G1[4 * g + 3] = g1.w;
+      }
+      L0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad0, Ba[0][0], L0, 0, 0, 0);
       L0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad1, Ba[0][1], L0, 0, 0, 0);
-      f16v L1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad0, Ba[1][0], zero16, 0, 0, 0);
+      L1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad0, Ba[1][0], L1, 0, 0, 0);
       L1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ad1, Ba[1][1], L1, 0, 0, 0);
-      f16v G0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag0, Bc[0][0], zero16, 0, 0, 0);
+      G0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag0, Bc[0][0], G0, 0, 0, 0);
       G0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag1, Bc[0][1], G0, 0, 0, 0);
-      f16v G1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag0, Bc[1][0], zero16, 0, 0, 0);
+      G1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag0, Bc[1][0], G1, 0, 0, 0);
       G1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ag1, Bc[1][1], G1, 0, 0, 0);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = 32 * rb + 8 * (v >> 2) + 4 * hh + (v & 3);
-        const float4 dd = st_dir[r];
-        const float4 gc = st_gc[r];
-        const float2 k0 = st_k[ks0][r], k1 = st_k[ks1][r];
-        const float vw0 = __builtin_amdgcn_exp2f(L0[v] - k0.x), vw1 = __builtin_amdgcn_exp2f(L1[v] - k1.x);
-        const float gl0 = vw0 * (G0[v] - k0.y), gl1 = vw1 * (G1[v] - k1.y);
-        sa[0][0] += gl0 * dd.x; sa[0][1] += gl0 * dd.y; sa[0][2] += gl0 * dd.z;
-        sa[1][0] += gl1 * dd.x; sa[1][1] += gl1 * dd.y; sa[1][2] += gl1 * dd.z;
-        sc[0][0] += vw0 * gc.x; sc[0][1] += vw0 * gc.y; sc[0][2] += vw0 * gc.z;
-        sc[1][0] += vw1 * gc.x; sc[1][1] += vw1 * gc.y; sc[1][2] += vw1 * gc.z;
+      for (int g = 0; g < 4; ++g) {
+        // the direction and dL/dc components lane % 4 of four records of the
+        // lane's half
+        const int r = 32 * rb + 8 * g + 4 * hh;
+        float dd[4], gc[4];
+        *reinterpret_cast<float4*>(dd) = *reinterpret_cast<const float4*>(&st_dir[lane & 3][r]);
+        *reinterpret_cast<float4*>(gc) = *reinterpret_cast<const float4*>(&st_gc[lane & 3][r]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int v = 4 * g + j;
+          const float vw0 = __builtin_amdgcn_exp2f(L0[v]), vw1 = __builtin_amdgcn_exp2f(L1[v]);
+          const float gl0 = vw0 * G0[v], gl1 = vw1 * G1[v];
+          sa[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(gl0, dd[j], sa[0], 0, 0, 0);
+          sa[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(gl1, dd[j], sa[1], 0, 0, 0);
+          sc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(vw0, gc[j], sc[0], 0, 0, 0);
+          sc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(vw1, gc[j], sc[1], 0, 0, 0);
+        }
       }
     }
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
 
-  // flush
+  // flush: lane t adds up sum t over the lanes (each starts at another one)
   for (int t = lane; t < NSUM; t += BWD_THREADS) {
-    const float v = acc[t];
+    const int2 at = acc_slot(t);
+    const float* p = reinterpret_cast<const float*>(acc[at.x]) + at.y;
+    float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int i = 0; i < 64; i += 4) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s4[j] += p[4 * ((t + i + j) & 63)];
+    }
+    const float v = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     if (v == 0.0f) continue;
     float* dst = nullptr;
     if (t < 3) dst = G.p ? G.p + 3 * (int64_t)ci + t : nullptr;
@@ -839,29 +960,30 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     }
     if (dst) atomicAdd(dst, v);
   }
-  if (contribution && lane == 0 && acc[ISTAT] != 0.0f) atomicAdd(contribution + ci, acc[ISTAT]);
-  // the two record halves of each site-axis pair: after the swap lane l
-  // holds the pair km = l (cb 0 in the lower half, cb 1 in the upper)
-  float va[3], vc[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(sa[0][c]), __float_as_uint(sa[1][c]), false, false);
-    va[c] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(sc[0][c]), __float_as_uint(sc[1][c]), false, false);
-    vc[c] = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  if (contribution) {
+    for (int o = 32; o > 0; o >>= 1) ta_sum += __shfl_xor(ta_sum, o, 64);
+    if (lane == 0 && ta_sum != 0.0f) atomicAdd(contribution + ci, ta_sum);
   }
   if (G.tex) {
-    float* gt = G.tex + (int64_t)ci * KD * TEXW + km * TEXW;
+    // the two record halves of each site-axis pair: after the swap lane
+    // 4 b + j holds component j of km = 4 b + i (cb 0 in the lower half of the
+    // lanes, cb 1 in the upper)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (va[c] != 0.0f) atomicAdd(gt + 3 + 3 * mm + c, va[c]);
-      if (vc[c] != 0.0f) atomicAdd(gt + 3 + 3 * MA + 3 * mm + c, vc[c]);
+    for (int i = 0; i < 4; ++i) {
+      const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(sa[0][i]), __float_as_uint(sa[1][i]), false, false);
+      const float va = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+      const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(sc[0][i]), __float_as_uint(sc[1][i]), false, false);
+      const float vc = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+      const int km = 4 * (lane >> 2) + i, j = lane & 3;
+      float* gt = G.tex + (int64_t)ci * KD * TEXW + (km >> 3) * TEXW + 3 + 3 * (km & 7) + j;
+      if (j < 3 && va != 0.0f) atomicAdd(gt, va);
+      if (j < 3 && vc != 0.0f) atomicAdd(gt + 3 * MA, vc);
     }
   }
   for (int f = lane; f < nfl; f += BWD_THREADS) {
     const int j = col[r0 + f];
     if (j < 0) continue;
-    const float4 v = facc[f];
+    const float4 v = make_float4(facc[f][0], facc[f][1], facc[f][2], facc[f][3]);
     if (G.p) {
       if (v.x != 0.0f) atomicAdd(G.p + 3 * (int64_t)j, v.x);
       if (v.y != 0.0f) atomicAdd(G.p + 3 * (int64_t)j + 1, v.y);
@@ -961,7 +1083,7 @@ pf_status backward_impl(const Scene& sc, const BwdState& st, const float* d_rgba
   PF_HIP_TRY(hipGetLastError());
   if (nchunks) {
     ProfScope ps("k_bwd_cell", s);
-    k_bwd_cell<<<nchunks, BWD_THREADS, 0, s>>>(st.cams_dev, st.rec.ri, st.rec.rf, order.p, chunks.p, sc.prm.p,
+    k_bwd_cell<<<nchunks, BWD_THREADS, 0, s>>>(st.cams_dev, st.ncam, st.rec.ri, st.rec.rf, order.p, chunks.p, sc.prm.p,
                                                 sc.prm.radius, sc.prm.normal, sc.prm.occ_logit, sc.prm.tex, sc.row,
                                                 sc.nrast, sc.col, sc.plane, sc.prm.sigma_scale, sc.prm.tau, g,
                                                 st.rec.rt, opt.lambda_normal, opt.contribution);

@@ -201,18 +201,22 @@ __device__ inline float dot3(float ax, float ay, float az, float bx, float by, f
 // Eq. svdisp / Eq. svrad).  The logits are shifted by tau*|u| and written as
 //   |u - s_k| - |u| = (|s_k|^2 - 2 u.s_k) / (|u - s_k| + |u|),
 // which keeps them accurate when u is far from the sites (grazing rays).
-template <typename FP>
-__device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w) {
+// STRIDE: floats from one site's (s, d) to the next; dist (if given): the
+// sites' |u - s_k| - |u|.
+template <int STRIDE = TEXW, typename FP>
+__device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w, float* dist_k = nullptr) {
   const float un = fsqrt(dot2(ux, ux, uy, uy));
   float mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < KD; ++k) {
-    const float sx = tx[k * TEXW + 0], sy = tx[k * TEXW + 1];
+    const float sx = tx[k * STRIDE + 0], sy = tx[k * STRIDE + 1];
     const float ex = ux - sx, ey = uy - sy;
     const float dist = fsqrt(dot2(ex, ex, ey, ey));
     const float num = fmaf(-2.0f, dot2(ux, sx, uy, sy), dot2(sx, sx, sy, sy));
     const float den = dist + un;
-    const float e = den > 0.0f ? num * frcp(den) : 0.0f;
+    const float q = num * frcp(den);   // (unconditional, so that the choice is no branch)
+    const float e = den > 0.0f ? q : 0.0f;
+    if (dist_k) dist_k[k] = e;
     w[k] = -tau * e;
     mx = fmaxf(mx, w[k]);
   }
