@@ -626,18 +626,25 @@ struct RasterCounts {
 // two) in plan[PLAN_LIST ...], plan[PLAN_COUNT] of them; plan[PLAN_NEXT] is the
 // queue of k_raster_split, zeroed here.
 //
-// With t the length, S(t) the entries of all lists up to t and SLOTS the tiles
-// that the chip holds at once, k_raster takes about max(CHAIN t, S(t) / SLOTS):
-// its longest list, walked by one wave per quadrant, or its share of the
-// whole; k_raster_split takes about SPLIT_COST (S - S(t)) / SLOTS for the rest,
-// its waves being less full.  The t of the least sum is taken.  (CHAIN and
-// SPLIT_COST from whole launches through either kernel: 10.5 ms or 1.0 ms for
-// 256x256 at 1,048,576 cells, 256 tiles; 2.25 or 2.06 ms, 1.83 ms as planned,
-// for 1280x720 at 262,144; 29.7 or 52.8 ms for 8 views of 1600x1066 at
-// 1,048,576, where the plan keeps k_raster.)
+// The cost of a launch that leaves lists up to length t to k_raster is taken as
+//   max(CHAIN t, D + CHAIN_SHARE CHAIN t) + S,
+// D the cost in k_raster of the lists up to t (DENSE_TILE + DENSE_ENTRY len each)
+// and S that in k_raster_split of the others (SPLIT_TILE + SPLIT_ENTRY len, less per
+// entry beyond SPLIT_KNEE): k_raster's longest list is walked by one wave per
+// quadrant, half of it while the others run, and it is cheap per tile;
+// k_raster_split works off one quadrant per CU at a time, which costs it more
+// per tile and per entry, but a list is sixteen times shorter.  The t of the
+// least cost is taken.  The constants (microseconds) are fitted to 43 launches of
+// 1k to 1M cells, 100x100 to 1920x1080, one to eight views, each through either
+// kernel alone: of 128x128 at 1,024 cells 0.165 or 0.054 ms, of 256x256 at
+// 1,048,576 6.6 or 0.71, of four mixed views up to 1920x1080 there 38 or 9.0, of
+// 1280x720 at 262,144 1.69 or 1.52 (1.26 as planned); of 2 views of 1027x1048 at
+// 2,561 0.34 or 0.49, of 3 of 1920x1080 at 60,000 2.6 or 5.6, of 8 of 1600x1066
+// at 1,048,576 24 or 41.
 constexpr int PLAN_LEN = 0, PLAN_COUNT = 1, PLAN_NEXT = 2, PLAN_LIST = 4;
 constexpr int PLAN_THREADS = 1024, PLAN_CLASSES = 256;
-constexpr float SLOTS = 256.0f * 7.0f, CHAIN = 1.5f, SPLIT_COST = 1.5f;
+constexpr float CHAIN = 2.5f, CHAIN_SHARE = 0.5f, DENSE_TILE = 0.02f, DENSE_ENTRY = 2.75e-3f;
+constexpr float SPLIT_TILE = 0.118f, SPLIT_ENTRY = 4.5e-3f, SPLIT_KNEE = 100.0f, SPLIT_LONG = 2.7e-3f;
 
 // Length class: lengths below 16 by themselves, then eight classes per power
 // of two; class_max is the largest length of a class.
@@ -657,7 +664,8 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_split_plan(const uint32_t* __r
   constexpr int REP = 8;   // copies of the histogram (fewer lanes meet on one word)
   __shared__ uint32_t s_n[REP][PLAN_CLASSES], s_sum[REP][PLAN_CLASSES];
   __shared__ uint32_t s_pos[PLAN_CLASSES];
-  __shared__ uint32_t s_part[4][2];
+  __shared__ uint32_t s_part[4];
+  __shared__ float s_partc[4][2];
   __shared__ float s_cost[4];
   __shared__ int s_cls[4], s_best;
   __shared__ uint32_t s_count;
@@ -689,38 +697,45 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_split_plan(const uint32_t* __r
   __syncthreads();
   // a thread per class: prefix sums of the lists and their entries, and the
   // least cost with its class
-  uint32_t n = 0, len = 0, n_in = 0, len_in = 0;
+  uint32_t n = 0, n_in = 0;
+  float dense = 0.0f, split = 0.0f;   // of the lists up to the class, either way
   if (t < PLAN_CLASSES) {
+    uint32_t sum = 0;
     for (int r = 0; r < REP; ++r) {
       n += s_n[r][t];
-      len += s_sum[r][t];
+      sum += s_sum[r][t];
     }
+    const float fn = (float)n, fl = (float)sum, head = fminf(fl, fn * SPLIT_KNEE);
     n_in = n;
-    len_in = len;
+    dense = DENSE_TILE * fn + DENSE_ENTRY * fl;
+    split = SPLIT_TILE * fn + SPLIT_ENTRY * head + SPLIT_LONG * (fl - head);
     for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t a = __shfl_up(n_in, d, 64), b = __shfl_up(len_in, d, 64);
+      const uint32_t a = __shfl_up(n_in, d, 64);
+      const float b = __shfl_up(dense, d, 64), c = __shfl_up(split, d, 64);
       if (lane >= d) {
         n_in += a;
-        len_in += b;
+        dense += b;
+        split += c;
       }
     }
     if (lane == 63) {
-      s_part[wave][0] = n_in;
-      s_part[wave][1] = len_in;
+      s_part[wave] = n_in;
+      s_partc[wave][0] = dense;
+      s_partc[wave][1] = split;
     }
   }
   __syncthreads();
-  const uint32_t n_all = s_part[0][0] + s_part[1][0] + s_part[2][0] + s_part[3][0];
-  const uint32_t len_all = s_part[0][1] + s_part[1][1] + s_part[2][1] + s_part[3][1];
+  const uint32_t n_all = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+  const float split_all = ((s_partc[0][1] + s_partc[1][1]) + s_partc[2][1]) + s_partc[3][1];
   if (t < PLAN_CLASSES) {
     for (int w = 0; w < wave; ++w) {
-      n_in += s_part[w][0];
-      len_in += s_part[w][1];
+      n_in += s_part[w];
+      dense += s_partc[w][0];
+      split += s_partc[w][1];
     }
     // (class 0, no lists of any length: everything is split)
-    float cost = n || t == 0 ? fmaxf(CHAIN * (float)class_max(t), (float)len_in / SLOTS) +
-                                   SPLIT_COST * (float)(len_all - len_in) / SLOTS
-                             : INFINITY;
+    const float chain = CHAIN * (float)class_max(t);
+    float cost = n || t == 0 ? fmaxf(chain, dense + CHAIN_SHARE * chain) + (split_all - split) : INFINITY;
     int cls = t;
     for (int o = 32; o > 0; o >>= 1) {
       const float c2 = __shfl_xor(cost, o, 64);
