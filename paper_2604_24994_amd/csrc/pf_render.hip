@@ -197,6 +197,7 @@ __global__ void k_view_count(const ViewDev* __restrict__ views, const float4* __
   Cone k;
   uint32_t c = 0;
   const int mode = cell_rect(v, ball[i], x0, x1, y0, y1, k);
+  if (o == 0) cnt[(int64_t)gridDim.y * n] = 0;   // (the scan's last entry)
   if (mode == 1) {
     c = (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
   } else if (mode == 2) {
@@ -274,66 +275,75 @@ __global__ void __launch_bounds__(256) k_view_emit(const ViewDev* __restrict__ v
   }
 }
 
-// One workgroup per listed (view, cell): its threads test the tiles of the
-// view in parallel.
+// One workgroup per listed (view, cell), in turn: its threads test the tiles of
+// the view in parallel.
 __global__ void __launch_bounds__(256) k_cone_count(const ViewDev* __restrict__ views,
                                                     const float4* __restrict__ ball, int64_t n,
                                                     const uint32_t* __restrict__ cone_list,
+                                                    const uint32_t* __restrict__ cone_n,
                                                     uint32_t* __restrict__ cnt) {
   __shared__ uint32_t part[4];
-  const uint32_t o = cone_list[blockIdx.x];
-  const int64_t i = (int64_t)(o % (uint64_t)n);
-  const ViewArgs& v = views[o / (uint64_t)n].v;
-  int x0, x1, y0, y1;
-  Cone k;
-  (void)cell_rect(v, ball[i], x0, x1, y0, y1, k);
-  const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
-  uint32_t c = 0;
-  for (int t = threadIdx.x; t < nt; t += 256) c += cone_tile(v.cam, k, x0 + t % tw, y0 + t / tw) ? 1u : 0u;
-  for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) cnt[o] = part[0] + part[1] + part[2] + part[3];
+  const uint32_t total = *cone_n;
+  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    const uint32_t o = cone_list[b];
+    const int64_t i = (int64_t)(o % (uint64_t)n);
+    const ViewArgs& v = views[o / (uint64_t)n].v;
+    int x0, x1, y0, y1;
+    Cone k;
+    (void)cell_rect(v, ball[i], x0, x1, y0, y1, k);
+    const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
+    uint32_t c = 0;
+    for (int t = threadIdx.x; t < nt; t += 256) c += cone_tile(v.cam, k, x0 + t % tw, y0 + t / tw) ? 1u : 0u;
+    for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[o] = part[0] + part[1] + part[2] + part[3];
+    __syncthreads();
+  }
 }
 
 __global__ void __launch_bounds__(256) k_cone_emit(const ViewDev* __restrict__ views, const float4* __restrict__ ball, int64_t n,
                                                    const uint32_t* __restrict__ off, const uint32_t* __restrict__ key,
                                                    const uint32_t* __restrict__ cone_list,
+                                                   const uint32_t* __restrict__ cone_n,
                                                    uint32_t* __restrict__ ptile, unsigned long long* __restrict__ pval,
                                                    uint32_t* __restrict__ tile_cnt) {
   __shared__ uint32_t wsum[4];
-  const uint32_t o = cone_list[blockIdx.x];
-  const int64_t i = (int64_t)(o % (uint64_t)n);
-  const ViewDev& vd = views[o / (uint64_t)n];
-  int x0, x1, y0, y1;
-  Cone k;
-  (void)cell_rect(vd.v, ball[i], x0, x1, y0, y1, k);
-  const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
-  const unsigned long long val = ((unsigned long long)key[o] << 32) | (uint32_t)i;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint32_t base = off[o];
-  for (int t0 = 0; t0 < nt; t0 += 256) {
-    const int t = t0 + threadIdx.x;
-    const int tx = x0 + t % tw, ty = y0 + t / tw;
-    const bool pass = t < nt && cone_tile(vd.v.cam, k, tx, ty);
-    const uint64_t m = __ballot(pass);
-    if (lane == 0) wsum[wv] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    for (int w = 0; w < 4; ++w) {
-      before += w < wv ? wsum[w] : 0u;
-      total += wsum[w];
+  const uint32_t ncone = *cone_n;
+  for (uint32_t b = blockIdx.x; b < ncone; b += gridDim.x) {
+    const uint32_t o = cone_list[b];
+    const int64_t i = (int64_t)(o % (uint64_t)n);
+    const ViewDev& vd = views[o / (uint64_t)n];
+    int x0, x1, y0, y1;
+    Cone k;
+    (void)cell_rect(vd.v, ball[i], x0, x1, y0, y1, k);
+    const int tw = x1 - x0 + 1, nt = tw * (y1 - y0 + 1);
+    const unsigned long long val = ((unsigned long long)key[o] << 32) | (uint32_t)i;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t base = off[o];
+    for (int t0 = 0; t0 < nt; t0 += 256) {
+      const int t = t0 + threadIdx.x;
+      const int tx = x0 + t % tw, ty = y0 + t / tw;
+      const bool pass = t < nt && cone_tile(vd.v.cam, k, tx, ty);
+      const uint64_t m = __ballot(pass);
+      if (lane == 0) wsum[wv] = (uint32_t)__popcll(m);
+      __syncthreads();
+      uint32_t before = 0, total = 0;
+      for (int w = 0; w < 4; ++w) {
+        before += w < wv ? wsum[w] : 0u;
+        total += wsum[w];
+      }
+      if (pass) {
+        const uint32_t pos = base + before + (uint32_t)__popcll(m & lt);
+        const uint32_t tile = (uint32_t)(vd.tile_base + ty * vd.v.tiles_x + tx);
+        ptile[pos] = tile;
+        pval[pos] = val;
+        atomicAdd(&tile_cnt[tile], 1u);
+      }
+      base += total;
+      __syncthreads();
     }
-    if (pass) {
-      const uint32_t pos = base + before + (uint32_t)__popcll(m & lt);
-      const uint32_t tile = (uint32_t)(vd.tile_base + ty * vd.v.tiles_x + tx);
-      ptile[pos] = tile;
-      pval[pos] = val;
-      atomicAdd(&tile_cnt[tile], 1u);
-    }
-    base += total;
-    __syncthreads();
   }
 }
 
@@ -1618,12 +1628,49 @@ int64_t view_tiles(const pf_camera& c) {
   return (int64_t)((c.width + TILE - 1) / TILE) * ((c.height + TILE - 1) / TILE);
 }
 
+namespace {
+
+// Consecutive arrays in one allocation, each on a 256-byte boundary.
+struct Arena {
+  int64_t bytes = 0;
+  int64_t add(int64_t count, int64_t size) {
+    const int64_t at = bytes;
+    bytes += (std::max<int64_t>(count, 1) * size + 255) & ~(int64_t)255;
+    return at;
+  }
+};
+
+// A group's arrays that are sized by its cells and tiles, and those sized by
+// its pairs: two allocations (an allocation's release records an event; with one
+// for each of the thirteen arrays the releases of a small render took as long as
+// its kernels).  The arrays that start as zeros are neighbours.
+struct GroupLayout {
+  Arena fixed, pairs;
+  int64_t views, cnt, key, off, cone_list, plan, toff, zero, tcnt, fill, cone_n, zero_end, ptile, pval, sorted;
+  GroupLayout(int64_t nvc, int nv, int64_t ntiles, int64_t np) {
+    views = fixed.add(nv, sizeof(ViewDev));
+    cnt = fixed.add(nvc + 1, 4);
+    key = fixed.add(nvc, 4);
+    off = fixed.add(nvc + 1, 4);
+    cone_list = fixed.add(nvc, 4);
+    plan = fixed.add(PLAN_LIST + ntiles, 4);
+    toff = fixed.add(ntiles + 1, 4);
+    zero = tcnt = fixed.add(ntiles + 1, 4);
+    fill = fixed.add(ntiles, 4);
+    cone_n = fixed.add(1, 4);
+    zero_end = fixed.bytes;
+    ptile = pairs.add(np, 4);
+    pval = pairs.add(np, 8);
+    sorted = pairs.add(np, 8);
+  }
+};
+
+}  // namespace
+
 int64_t raster_group_bytes(int64_t n, int nv, int64_t ntiles, int64_t np) {
-  auto b = [](int64_t count, int64_t size) { return std::max<int64_t>(count, 1) * size; };
   const int64_t nvc = (int64_t)nv * n;
-  return b(nv, sizeof(ViewDev)) + b(nvc + 1, 4) * 2 + b(nvc, 4) * 2 + b(ntiles + 1, 4) * 2 + b(ntiles, 4) +
-         b(PLAN_LIST + ntiles, 4) +
-         b(1, 4) + scan_scratch_bytes(nvc + 1) + scan_scratch_bytes(ntiles + 1) + b(np, 4) + b(np, 8) * 2;
+  const GroupLayout l(nvc, nv, ntiles, np);
+  return l.fixed.bytes + l.pairs.bytes + scan_scratch_bytes(nvc + 1) + scan_scratch_bytes(ntiles + 1);
 }
 
 namespace {
@@ -1634,12 +1681,15 @@ struct Group {
   int c0 = 0, nv = 0;
   int64_t ntiles = 0, tiles_before = 0, pix_before = 0;
   uint32_t np = 0;
-  Buf<ViewDev> views;
-  Buf<uint32_t> cnt, key, off, tcnt, toff, fill, cone_list, cone_n, ptile, plan;
-  Buf<unsigned long long> pval, sorted;
-  explicit Group(hipStream_t s)
-      : views(s), cnt(s), key(s), off(s), tcnt(s), toff(s), fill(s), cone_list(s), cone_n(s), ptile(s), plan(s),
-        pval(s), sorted(s) {}
+  Buf<char> fixed, pairs;
+  template <typename T>
+  struct Part {
+    T* p = nullptr;
+  };
+  Part<ViewDev> views;
+  Part<uint32_t> cnt, key, off, tcnt, toff, fill, cone_list, cone_n, ptile, plan;
+  Part<unsigned long long> pval, sorted;
+  explicit Group(hipStream_t s) : fixed(s), pairs(s) {}
 };
 
 // Cull and count (count_only: stops after the pair count), then emit,
@@ -1662,18 +1712,23 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   }
   G.ntiles = ntiles;
   const int64_t nvc = (int64_t)nv * n;
-  PF_HIP_TRY(G.views.alloc(nv));
+  {
+    const GroupLayout l(nvc, nv, ntiles, 0);
+    PF_HIP_TRY(G.fixed.alloc(l.fixed.bytes));
+    char* p = G.fixed.p;
+    G.views.p = (ViewDev*)(p + l.views);
+    G.cnt.p = (uint32_t*)(p + l.cnt);
+    G.key.p = (uint32_t*)(p + l.key);
+    G.off.p = (uint32_t*)(p + l.off);
+    G.cone_list.p = (uint32_t*)(p + l.cone_list);
+    G.plan.p = (uint32_t*)(p + l.plan);
+    G.toff.p = (uint32_t*)(p + l.toff);
+    G.tcnt.p = (uint32_t*)(p + l.tcnt);
+    G.fill.p = (uint32_t*)(p + l.fill);
+    G.cone_n.p = (uint32_t*)(p + l.cone_n);
+    PF_HIP_TRY(hipMemsetAsync(p + l.zero, 0, (size_t)(l.zero_end - l.zero), s));
+  }
   PF_HIP_TRY(hipMemcpyAsync(G.views.p, hv.data(), sizeof(ViewDev) * nv, hipMemcpyHostToDevice, s));
-  PF_HIP_TRY(G.cnt.alloc(nvc + 1));
-  PF_HIP_TRY(G.key.alloc(nvc));
-  PF_HIP_TRY(G.off.alloc(nvc + 1));
-  PF_HIP_TRY(G.tcnt.alloc(ntiles + 1));
-  PF_HIP_TRY(G.toff.alloc(ntiles + 1));
-  PF_HIP_TRY(G.fill.alloc(ntiles));
-  PF_HIP_TRY(G.plan.alloc(PLAN_LIST + ntiles));
-  PF_HIP_TRY(G.cone_list.alloc(nvc));
-  PF_HIP_TRY(G.cone_n.alloc(1));
-  PF_HIP_TRY(hipMemsetAsync(G.cone_n.p, 0, sizeof(uint32_t), s));
   const dim3 g((unsigned)((n + 255) / 256), (unsigned)nv);
   {
     ProfScope ps("k_view_count", s);
@@ -1681,14 +1736,10 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
                                    G.cone_n.p);
   }
   PF_HIP_TRY(hipGetLastError());
-  uint32_t ncone = 0;
-  PF_HIP_TRY(hipMemcpyAsync(&ncone, G.cone_n.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  PF_HIP_TRY(hipStreamSynchronize(s));
-  if (ncone) {
-    k_cone_count<<<ncone, 256, 0, s>>>(G.views.p, sc.ball, n, G.cone_list.p, G.cnt.p);
-    PF_HIP_TRY(hipGetLastError());
-  }
-  PF_HIP_TRY(hipMemsetAsync(G.cnt.p + nvc, 0, sizeof(uint32_t), s));
+  // (their number stays on the device: the workgroups share what there is)
+  const unsigned gcone = (unsigned)std::min<int64_t>(nvc, 1024);
+  k_cone_count<<<gcone, 256, 0, s>>>(G.views.p, sc.ball, n, G.cone_list.p, G.cone_n.p, G.cnt.p);
+  PF_HIP_TRY(hipGetLastError());
   PF_HIP_TRY(exclusive_scan_u32(G.cnt.p, G.off.p, nvc + 1, nullptr, s));
   uint32_t np = 0;
   PF_HIP_TRY(hipMemcpyAsync(&np, G.off.p + nvc, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -1697,17 +1748,18 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   double ppc = (double)np / (double)nvc;   // sizing hint (renders may run on several threads)
   __atomic_store(&sc.pairs_per_cell, &ppc, __ATOMIC_RELAXED);
   if (count_only) return PF_OK;
-  PF_HIP_TRY(G.ptile.alloc(np));
-  PF_HIP_TRY(G.pval.alloc(np));
-  PF_HIP_TRY(G.sorted.alloc(np));
-  PF_HIP_TRY(hipMemsetAsync(G.tcnt.p, 0, sizeof(uint32_t) * (ntiles + 1), s));
-  PF_HIP_TRY(hipMemsetAsync(G.fill.p, 0, sizeof(uint32_t) * ntiles, s));
+  {
+    const GroupLayout l(nvc, nv, ntiles, np);
+    PF_HIP_TRY(G.pairs.alloc(l.pairs.bytes));
+    G.ptile.p = (uint32_t*)(G.pairs.p + l.ptile);
+    G.pval.p = (unsigned long long*)(G.pairs.p + l.pval);
+    G.sorted.p = (unsigned long long*)(G.pairs.p + l.sorted);
+  }
   {
     ProfScope ps("k_view_emit", s);
     k_view_emit<<<g, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.ptile.p, G.pval.p, G.tcnt.p);
-    if (ncone)
-      k_cone_emit<<<ncone, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.cone_list.p, G.ptile.p,
-                                        G.pval.p, G.tcnt.p);
+    k_cone_emit<<<gcone, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.cone_list.p, G.cone_n.p, G.ptile.p,
+                                      G.pval.p, G.tcnt.p);
   }
   PF_HIP_TRY(hipGetLastError());
   PF_HIP_TRY(exclusive_scan_u32(G.tcnt.p, G.toff.p, ntiles + 1, nullptr, s));

@@ -277,6 +277,35 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_block_apply(const uint32_t* in
   if (total_dev && blockIdx.x == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) *total_dev = run;
 }
 
+// The whole scan in one launch, for a few blocks and in != out: every block adds
+// up the entries before it by itself (small renders and scenes are bound by
+// launches: three launches and an allocation otherwise).
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_few(const uint32_t* __restrict__ in, int64_t n,
+                                                           uint32_t* __restrict__ out, uint32_t* total_dev) {
+  const int64_t first = (int64_t)blockIdx.x * SCAN_TILE;
+  uint32_t before = 0;
+  for (int64_t i = threadIdx.x; i < first; i += SCAN_THREADS) before += in[i];
+  uint32_t offs;
+  block_exclusive_scan(before, &offs);
+  const int64_t base = first + (int64_t)threadIdx.x * SCAN_ITEMS;
+  uint32_t v[SCAN_ITEMS];
+  uint32_t s = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    v[k] = (base + k < n) ? in[base + k] : 0u;
+    s += v[k];
+  }
+  uint32_t tot;
+  uint32_t run = block_exclusive_scan(s, &tot) + offs;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    if (base + k < n) out[base + k] = run;
+    run += v[k];
+  }
+  if (total_dev && blockIdx.x == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) *total_dev = run;
+}
+constexpr int64_t SCAN_FEW = 16;   // blocks (32,768 entries): at most 120 reads per thread for the entries before
+
 }  // namespace
 
 int64_t scan_scratch_bytes(int64_t n) {
@@ -297,6 +326,10 @@ hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
     return hipSuccess;
   }
   const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+  if (nb > 1 && nb <= SCAN_FEW && (in + n <= out || out + n <= in)) {
+    k_scan_few<<<(unsigned)nb, SCAN_THREADS, 0, s>>>(in, n, out, total_dev);
+    return hipGetLastError();
+  }
   if (nb == 1) {
     k_block_apply<<<1, SCAN_THREADS, 0, s>>>(in, n, nullptr, out, total_dev);
     return hipGetLastError();
