@@ -366,7 +366,7 @@ __device__ inline void len_rlen(double x2, double& len, double& rlen) {
 // (in float64 the kernel took 6% longer; against the oracle adjoint the
 // worst per-component error over the GPU gradient tests rose from 7e-6 to
 // 1.6e-4, on the normal of one small scene, the others unchanged).
-__device__ inline void sv_backward(const float* site, const float* off, double ux_d, double uy_d, const double* ge,
+__device__ inline void sv_backward(const float* site, double ux_d, double uy_d, const double* ge,
                                    double& gux, double& guy, AccRow* acc, bool valid) {
   const float ux = (float)ux_d, uy = (float)uy_d;
   const float u2 = ux * ux + uy * uy;
@@ -386,8 +386,10 @@ __device__ inline void sv_backward(const float* site, const float* off, double u
       const float rq = __builtin_amdgcn_rsqf(d2);
       const float rd = d2 > 0.0f ? rq : 0.0f;
       const float dist = d2 * rd;
-      // both forms, and a choice without a branch; |u - s| - |u| as in the weights
-      const float e = off[k];
+      // both forms, and a choice without a branch.  (|u - s| - |u| with this
+      // function's own distances: taken from the weights', 1 ms faster over the
+      // kernel's 30, rays that graze the face lost digits of the normal's gradient.)
+      const float e = (sx * sx + sy * sy - 2.0f * (ux * sx + uy * sy)) * frcp(dist + un);   // |u - s| - |u|
       const float f = rd * iun;
       const float ax = (-ux * e - sx * un) * f, ay = (-uy * e - sy * un) * f;
       const bool both = un > 0.0f && dist > 0.0f;
@@ -407,13 +409,12 @@ __device__ inline void sv_backward(const float* site, const float* off, double u
 // 5% slower), and eight workgroups' LDS per CU.
 // The kernel is bound by the vector instructions it issues (77% of the SIMDs'
 // cycles) and, with two waves to hide them, by the waits between.  37.1 ms for
-// the 8 views of 1600x1066 of a training step at 1,048,576 cells became 30.5:
-// the sites' lobes and the transposed sums as 4x4x1 FP32 MFMAs, the shifts and
-// dL/dw as initial values of the transposed MFMAs, sums kept per lane, choices
-// instead of branches (together 37.1 -> 36.4, the waits having become the bound);
+// the 8 views of 1600x1066 of a training step at 1,048,576 cells became 31.3:
+// the sites' lobes and the transposed sums as 4x4x1 FP32 MFMAs, sums kept per
+// lane, choices instead of branches (together 37.1 -> 36.4, the waits having become the bound);
 // then planes, cameras, axes and colours in LDS, the face sums without LDS atomics
-// and 16-byte LDS reads (-> 32.3), the sites' distances shared by weights and
-// derivatives and a pixel's row without an integer division (-> 30.5).
+// and 16-byte LDS reads (-> 32.3), the transposed products' initial values and a
+// pixel's row without an integer division (-> 31.3).
 __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) k_bwd_cell(
     const pf_camera* __restrict__ cams, int ncam, const int4* __restrict__ ri, const float4* __restrict__ rf,
     const int32_t* __restrict__ order, const int4* __restrict__ chunks, const float* __restrict__ prm_p,
@@ -623,8 +624,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     const double ubx = qt1 + sbar * dt1, uby = qt2 + sbar * dt2;
     double delta = 0.0;
     float wd[KD];   // displacement weights at ubar
-    float od[KD], our[KD];   // the sites' |u - s_k| - |u|
-    sv_weights<3>(site, (float)ubx, (float)uby, tau, wd, od);
+    sv_weights<3>(site, (float)ubx, (float)uby, tau, wd);
 #pragma unroll
     for (int k = 0; k < KD; ++k) delta += (double)wd[k] * (double)site[3 * k + 2];
     const double sxx = (delta - qn) * idn;
@@ -657,7 +657,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     // colours sv_k(d) and the softmax backward of the weights
     float wr[KD];
     renew();
-    sv_weights<3>(site, (float)ux, (float)uy, tau, wr, our);
+    sv_weights<3>(site, (float)ux, (float)uy, tau, wr);
     double sum_wg = 0.0;
     float gwr[KD];
     const float gx = fx * LOG2E_F, gy = fy * LOG2E_F, gz = fz * LOG2E_F;
@@ -711,7 +711,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int k = 0; k < KD; ++k) ge[k] = -(double)tau * (double)wr[k] * ((double)gwr[k] - sum_wg);
       renew();
-      sv_backward(site, our, ux, uy, ge, gux, guy, acc, valid);
+      sv_backward(site, ux, uy, ge, gux, guy, acc, valid);
     }
     // u = (qt1 + S dt1, qt2 + S dt2)
     double g_qt1 = gux, g_qt2 = guy, g_dt1 = gux * S, g_dt2 = guy * S;
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int k = 0; k < KD; ++k) ge[k] = -(double)tau * (double)wd[k] * (gw[k] - sum_w);
       renew();
-      sv_backward(site, od, ubx, uby, ge, gubx, guby, acc, valid);
+      sv_backward(site, ubx, uby, ge, gubx, guby, acc, valid);
       // ubar = (qt1 + sbar dt1, qt2 + sbar dt2), sbar = -qn/den
       g_qt1 += gubx;
       g_qt2 += guby;

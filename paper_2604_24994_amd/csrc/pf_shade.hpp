@@ -201,10 +201,9 @@ __device__ inline float dot3(float ax, float ay, float az, float bx, float by, f
 // Eq. svdisp / Eq. svrad).  The logits are shifted by tau*|u| and written as
 //   |u - s_k| - |u| = (|s_k|^2 - 2 u.s_k) / (|u - s_k| + |u|),
 // which keeps them accurate when u is far from the sites (grazing rays).
-// STRIDE: floats from one site's (s, d) to the next; dist (if given): the
-// sites' |u - s_k| - |u|.
+// STRIDE: floats from one site's (s, d) to the next.
 template <int STRIDE = TEXW, typename FP>
-__device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w, float* dist_k = nullptr) {
+__device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w) {
   const float un = fsqrt(dot2(ux, ux, uy, uy));
   float mx = -INFINITY;
 #pragma unroll
@@ -216,7 +215,6 @@ __device__ inline void sv_weights(FP tx, float ux, float uy, float tau, float* w
     const float den = dist + un;
     const float q = num * frcp(den);   // (unconditional, so that the choice is no branch)
     const float e = den > 0.0f ? q : 0.0f;
-    if (dist_k) dist_k[k] = e;
     w[k] = -tau * e;
     mx = fmaxf(mx, w[k]);
   }
