@@ -49,17 +49,18 @@ FLOPS_BWD_PER_CONTRIB = 5100
 # (FETCH_SIZE reads 0.5 GiB: x2.0; WRITE_SIZE reads 1 GiB: x1.0).  Valid only
 # for the kernel sources with these hashes; otherwise the bench reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-_SRC_SHADE = {"pf_shade.hpp": "fafcd449bb434a34", "pf_internal.hpp": "cf1b6d1fee18a09d",
+_SRC_SHADE = {"pf_shade.hpp": "db8c5ed80bf9de2b", "pf_internal.hpp": "3defdcb24a091f30",
               "pf_record.hpp": "d8db4e8267ff8479"}
 TRAFFIC = {
-    "k_bwd_cell": {"fetch_kib": 7865870.9, "write_kib": 2407941.7,
-                   "sources": {"pf_backward.hip": "fb3e4556d9e14fb8", **_SRC_SHADE}},
-    "k_raster_store": {"fetch_kib": 17647219.1, "write_kib": 11375718.7,
-                       "sources": {"pf_render.hip": "1e3097ce83ad03bf", **_SRC_SHADE}},
-    "k_trace": {"fetch_kib": 8362805.2, "write_kib": 46637.5,
-                "sources": {"pf_render.hip": "1e3097ce83ad03bf", **_SRC_SHADE}},
-    "k_clip": {"fetch_kib": 409452.2, "write_kib": 180425.5,
-               "sources": {"pf_build.hip": "60ddab952277c61e", "pf_internal.hpp": "cf1b6d1fee18a09d",
+    "k_bwd_cell": {"fetch_kib": 7794425.8, "write_kib": 2254580.4,
+                   "sources": {"pf_backward.hip": "916f23a88b23ad83", **_SRC_SHADE}},
+    # (k_raster and k_raster_split together)
+    "k_raster_store": {"fetch_kib": 17304732.8, "write_kib": 12163013.9,
+                       "sources": {"pf_render.hip": "a342415610c97a37", **_SRC_SHADE}},
+    "k_trace": {"fetch_kib": 4897602.8, "write_kib": 26650.0,
+                "sources": {"pf_render.hip": "a342415610c97a37", **_SRC_SHADE}},
+    "k_clip": {"fetch_kib": 480449.0, "write_kib": 173694.4,
+               "sources": {"pf_build.hip": "8e8ab9d979c5ebf9", "pf_internal.hpp": "3defdcb24a091f30",
                            "pf_record.hpp": "d8db4e8267ff8479"}},
 }
 
