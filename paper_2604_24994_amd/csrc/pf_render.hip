@@ -38,9 +38,35 @@ __device__ inline uint32_t order_key(float f) {
 
 constexpr double RECT_PAD = 1e-2;   // pixels
 
+// Pixels by which a ball's bounds on the image are widened.  A ray's direction
+// is M v (M the camera's 3x3 matrix), while the bounds come from v' = M^T e of
+// the centre e, which is M^-1 e + E M^-1 e with E = M^T M - 1: a rotation
+// rounded to float32 moves them by less than 1e-3 pixels, a matrix written with
+// a few digits, or with an axis scaled a little, by up to some pixels.  Where
+// the shift (|E| and the ray's own float32 rounding, times the pixels per unit
+// of angle at the image's corner) may reach half of RECT_PAD, the pad is a pixel.
+double rect_pad(const pf_camera& c) {
+  double e2 = 0.0;
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) {
+      double d = i == j ? -1.0 : 0.0;
+      for (int r = 0; r < 3; ++r) d += (double)c.c2w[4 * r + i] * (double)c.c2w[4 * r + j];
+      e2 += d * d;
+    }
+  double scale;
+  if (c.model == 0) {
+    const double x = std::max(std::fabs((double)c.cx), std::fabs(c.width - (double)c.cx)) / c.fx;
+    const double y = std::max(std::fabs((double)c.cy), std::fabs(c.height - (double)c.cy)) / c.fy;
+    scale = std::max(c.fx, c.fy) * (1.0 + x * x + y * y);
+  } else {
+    scale = c.f_fish * (double)c.theta_max / std::sin(std::min((double)c.theta_max, 3.0));
+  }
+  return (std::sqrt(e2) + 1.2e-7) * scale <= 0.5 * RECT_PAD ? RECT_PAD : 1.0;
+}
+
 // Tile rectangle of a ball (camera-space centre X,Y,Z, radius rho).
-__device__ bool ball_rect(const pf_camera& c, double X, double Y, double Z, double rho, int tiles_x, int tiles_y,
-                          int& x0, int& x1, int& y0, int& y1) {
+__device__ bool ball_rect(const pf_camera& c, double pad, double X, double Y, double Z, double rho, int tiles_x,
+                          int tiles_y, int& x0, int& x1, int& y0, int& y1) {
   const double W = c.width, H = c.height;
   double ulo, uhi, vlo, vhi;
   bool full = false;
@@ -107,9 +133,9 @@ __device__ bool ball_rect(const pf_camera& c, double X, double Y, double Z, doub
     return true;
   }
   // pixels whose centre (p + 1/2) may lie in [lo, hi] (a ball between two pixel
-  // centres has none); the pad covers the rounding of the float64 bounds
-  const double pxl = ceil(ulo - 0.5 - RECT_PAD), pxh = floor(uhi - 0.5 + RECT_PAD);
-  const double pyl = ceil(vlo - 0.5 - RECT_PAD), pyh = floor(vhi - 0.5 + RECT_PAD);
+  // centres has none), padded by rect_pad
+  const double pxl = ceil(ulo - 0.5 - pad), pxh = floor(uhi - 0.5 + pad);
+  const double pyl = ceil(vlo - 0.5 - pad), pyh = floor(vhi - 0.5 + pad);
   if (!(pxh >= 0.0 && pyh >= 0.0 && pxl <= W - 1 && pyl <= H - 1 && pxl <= pxh && pyl <= pyh)) return false;
   x0 = (int)fmax(0.0, floor(fmax(pxl, 0.0) / TILE));
   x1 = (int)fmin((double)(tiles_x - 1), floor(fmin(pxh, W - 1) / TILE));
@@ -121,6 +147,7 @@ __device__ bool ball_rect(const pf_camera& c, double X, double Y, double Z, doub
 struct ViewArgs {
   pf_camera cam;
   int tiles_x, tiles_y;
+  double pad;   // rect_pad
 };
 
 // One camera of a batched raster call: its tiles are numbered from
@@ -164,7 +191,7 @@ __device__ inline int cell_rect(const ViewArgs& v, const float4 g, int& x0, int&
   const double Y = m[1] * ex + m[5] * ey + m[9] * ez;
   const double Z = m[2] * ex + m[6] * ey + m[10] * ez;
   const double r = (double)g.w * (1.0 + 1e-5) + 1e-7;
-  if (!ball_rect(v.cam, X, Y, Z, r, v.tiles_x, v.tiles_y, x0, x1, y0, y1)) return 0;
+  if (!ball_rect(v.cam, v.pad, X, Y, Z, r, v.tiles_x, v.tiles_y, x0, x1, y0, y1)) return 0;
   if (v.cam.model == 0 && Z - r <= 1e-9 * (1.0 + fabs(Z))) {
     const double L = sqrt(X * X + Y * Y + Z * Z);
     if (L > r * (1.0 + 1e-9)) {
@@ -1752,6 +1779,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
     hv[v].v.cam = cam;
     hv[v].v.tiles_x = (cam.width + TILE - 1) / TILE;
     hv[v].v.tiles_y = (cam.height + TILE - 1) / TILE;
+    hv[v].v.pad = rect_pad(cam);
     hv[v].tile_base = ntiles;
     hv[v].pix_base = pix;
     hv[v].view_id = G.c0 + v;
@@ -1934,6 +1962,7 @@ pf_status trace_view(const Scene& sc, const pf_camera& cam, float t_min, int max
   v.cam = cam;
   v.tiles_x = (cam.width + TILE - 1) / TILE;
   v.tiles_y = (cam.height + TILE - 1) / TILE;
+  v.pad = 0.0;   // (no tile lists)
   const int64_t ntiles = tile_count >= 0 ? tile_count : (int64_t)v.tiles_x * v.tiles_y - tile_first;
   if (ntiles <= 0) return PF_OK;
   const int nb = (int)std::min<int64_t>(TRACE_START_BLOCKS, (n + 255) / 256);
