@@ -32,8 +32,9 @@
  *  - Parameters, images and gradients are caller-owned; the library keeps
  *    pointers to the parameter arrays inside a scene, so they must stay
  *    allocated and unchanged until pf_scene_destroy (re-build after changing
- *    them).  Library-owned memory (adjacency, per-view lists, forward state)
- *    is released by pf_scene_destroy / pf_state_release.
+ *    them; rgb and tex alone: see pf_build_scene).  Library-owned memory
+ *    (adjacency, per-view lists, forward state) is released by
+ *    pf_scene_destroy / pf_state_release.
  *  - Device memory of the library comes from the caller's allocator when one
  *    is set (pf_set_allocator), e.g. the framework's caching allocator, so
  *    that one allocator owns all memory.  Without one, the library keeps
@@ -167,8 +168,12 @@ typedef struct {
 /* Builds the face adjacency of the power diagram clipped to the domain box
    (the regular-triangulation adjacency the walk needs, appendix C; the
    raster uses the subset of faces within each cell's sphere, Sec. 3.2),
-   per-cell cull radii bounding the non-empty part of each bounded cell, and
-   empty-cell flags.  params (host) is copied; its arrays are referenced.
+   a ball per cell around the dense part of the bounded cell (from p, power,
+   radius, normal and the displacements in tex), and empty-cell flags.  Colours,
+   axes and detail sites in rgb and tex are read by each render as they are
+   then, and so are the displacements: a render that finds a face lifted above
+   the largest displacement it was built with bounds that cell by all of it,
+   which costs time, not pixels.  params (host) is copied; its arrays are referenced.
    opts (host) may be NULL.  Synchronises the stream (sizes the adjacency).
    A cell of zero density (occ_logit = -inf, e.g. a Steiner cell) whose power
    cell exceeds the face capacity (256 planes) is dropped: the build is
@@ -181,7 +186,7 @@ typedef struct {
 pf_status pf_build_scene(const pf_params* params, const pf_build_opts* opts,
                          void* stream, pf_scene** out);
 
-/* Rebuilds the adjacency, cull radii and flags of an existing scene for new
+/* Rebuilds the adjacency, balls and flags of an existing scene for new
    parameter values (the sites moved during training), keeping the scene's
    build options and sizing hints.  The previous adjacency seeds the new one
    (a cell starts from its previous neighbours, or from the sites that

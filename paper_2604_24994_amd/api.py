@@ -114,7 +114,9 @@ def build_scene(params, sigma_scale: float = 10.0, tau: float = 20.0, box=None, 
                 stream=None) -> Scene:
     """pf_build_scene.  ``params``: dict/object of cell arrays (moved to the
     GPU as float32 if needed).  ``box``: optional (min[3], max[3]) the domain
-    box must contain (e.g. trace camera centres)."""
+    box must contain (e.g. trace camera centres).  Later changes of the scene's
+    ``rgb`` and ``tex`` tensors in place show in the next render; all other
+    fields need ``update_scene``."""
     _require_cuda()
     lib = L.load()
     t = to_device_params(params)

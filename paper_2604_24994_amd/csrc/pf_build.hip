@@ -723,7 +723,8 @@ __device__ void write_witness(const Shared<SPL, PM>& S, const Poly<SPL>& P, int 
 }
 
 // A ball around the part of the cell that can contribute to an image: the
-// polytope where (x - p).n <= max(0, largest displacement), inside the sphere.
+// polytope where (x - p).n <= disp, inside the sphere, disp the sites' largest
+// displacement or 0.
 // (The displaced face lies within the sites' displacements, so the dense side
 // does not reach past that plane; a ray along the face counts the side below
 // the undisplaced one.)  Its corners are the vertices on that side and the
@@ -739,7 +740,7 @@ __device__ float4 dense_ball(const Shared<SPL, PM>& S, const EOT* eo, const Poly
   const double ax = normal[0], ay = normal[1], az = normal[2];
   const double inv = 1.0 / sqrt(ax * ax + ay * ay + az * az);
   const double nx = ax * inv, ny = ay * inv, nz = az * inv;
-  const double top = fmax((double)disp, 0.0) * (1.0 + 1e-5) + 1e-7 * (double)r;
+  const double top = (double)disp * (1.0 + 1e-5) + 1e-7 * (double)r;
   uint64_t above[SPL];
 #pragma unroll
   for (int s = 0; s < SPL; ++s) {
@@ -818,7 +819,8 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
                                              const int32_t* __restrict__ wwit, const float4* __restrict__ wsp,
                                              const int32_t* __restrict__ wspos, int64_t wn,
                                              int32_t* __restrict__ wit_out, const float* __restrict__ normal,
-                                             const float* __restrict__ tex, float4* __restrict__ ball) {
+                                             const float* __restrict__ tex, float4* __restrict__ ball,
+                                             float* __restrict__ ball_top) {
   constexpr bool LISTED = MODE >= 1, EO_HBM = MODE == 2;
   using EOT = typename std::conditional<(64 * SPL > 256), unsigned short, unsigned char>::type;
   static_assert(EO_HBM ? std::is_same<EOT, unsigned short>::value : true, "HBM edge table holds 16-bit slots");
@@ -1186,12 +1188,7 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
     return;
   }
   // the largest displacement of the cell's face (loaded here, used at the end)
-  // (unbounded where a detail site is not finite: its weights are no convex combination then)
-  float disp = -INFINITY;
-  if (lane < KD) {
-    const float* t = tex + ((int64_t)self * KD + lane) * TEXW;
-    disp = fabsf(t[0]) + fabsf(t[1]) + fabsf(t[2]) < INFINITY ? t[2] : INFINITY;
-  }
+  const float disp = lane < KD ? site_top(tex + ((int64_t)self * KD + lane) * TEXW) : -INFINITY;
   for (int q = lane; q < PM; q += 64) S.used[q] = 0;
   __syncthreads();
 #pragma unroll
@@ -1267,17 +1264,20 @@ __global__ void __launch_bounds__(64) k_clip(const float4* __restrict__ sp, cons
   viol = wave_max_d(viol);
   if (P.stale) update_bounds(S, P);
   const double R = sqrt(S.bd[BD_R2]);
-  const float dmax_f = wave_max_dpp(disp);
-  const float4 bl = dense_ball(S, eo, P, normal + 3 * (int64_t)self, dmax_f, (float)ri);
+  const float top = fmaxf(wave_max_dpp(disp), 0.0f);
+  const float4 bl = dense_ball(S, eo, P, normal + 3 * (int64_t)self, top, (float)ri);
   if (lane == 0) {
     counts[self] = base;
     nrast[self] = nr;
     const bool hidden = viol > ri;
-    cull[self] = hidden ? -1.0f : (float)fmin(ri, R * (1.0 + 1e-6));
-    // (the margin covers the rounding of the centre and of the pieces' float32 ends)
-    const double far = fabs(px) + fabs(py) + fabs(pz);
-    ball[self] = make_float4((float)(px + bl.x), (float)(py + bl.y), (float)(pz + bl.z),
-                             hidden || bl.w < 0.0f ? -1.0f : bl.w * (1.0f + 1e-4f) + (float)(1e-6 * far));
+    const float rcull = (float)fmin(ri, R * (1.0 + 1e-6));
+    cull[self] = hidden ? -1.0f : rcull;
+    float4 wide = widened_ball((float)(px + bl.x), (float)(py + bl.y), (float)(pz + bl.z), bl.w,
+                               fabs(px) + fabs(py) + fabs(pz));
+    if (hidden || bl.w < 0.0f) wide.w = -1.0f;
+    ball[self] = wide;
+    // (as large as the whole cell's, it does not depend on the displacements)
+    ball_top[self] = bl.w >= rcull ? INFINITY : top;
     flags[self] = 0;
   }
 }
@@ -1611,7 +1611,7 @@ pf_status connect_loss_impl(const Scene& sc, float lambda, const pf_grads& g, do
 }
 
 void free_scene(Scene* sc, hipStream_t s, bool async) {
-  void* ptrs[] = {sc->geo,  sc->nrm,    sc->cull, sc->ball,   sc->flags, sc->row,  sc->nrast, sc->col,
+  void* ptrs[] = {sc->geo,  sc->nrm,    sc->cull, sc->ball,   sc->ball_top, sc->flags, sc->row,  sc->nrast, sc->col,
                   sc->plane, sc->t_sp, sc->t_sidx, sc->t_srad, sc->t_lo, sc->t_hi, sc->wit, sc->tri};
   // synchronous: renders on any stream may still read the arrays
   if (!async) (void)hipDeviceSynchronize();
@@ -1620,6 +1620,7 @@ void free_scene(Scene* sc, hipStream_t s, bool async) {
   sc->geo = sc->nrm = nullptr;
   sc->cull = nullptr;
   sc->ball = nullptr;
+  sc->ball_top = nullptr;
   sc->flags = sc->row = sc->nrast = sc->col = nullptr;
   sc->plane = nullptr;
   sc->t_sp = sc->t_lo = sc->t_hi = nullptr;
@@ -1745,6 +1746,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
   // per-cell clipping
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->cull, sizeof(float) * n, s));
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->ball, sizeof(float4) * n, s));
+  PF_HIP_TRY(pf::pool_alloc((void**)&sc->ball_top, sizeof(float) * n, s));
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->flags, sizeof(int32_t) * n, s));
   PF_HIP_TRY(pf::pool_alloc((void**)&sc->wit, sizeof(int32_t) * WIT * n, s));
   PF_HIP_TRY(hipMemsetAsync(sc->wit, 0xFF, sizeof(int32_t) * WIT * n, s));
@@ -1837,7 +1839,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
                                                            bmax, prm.radius, nullptr, nullptr, faces_tmp.p, nullptr,
                                                            counts.p, sc->nrast, sc->cull, sc->flags, warm_row,
                                                            warm_col, warm_tri, warm_wit, sp.p, spos.p, n, sc->wit,
-                                                           prm.normal, prm.tex, sc->ball);
+                                                           prm.normal, prm.tex, sc->ball, sc->ball_top);
   }
   PF_HIP_TRY(hipGetLastError());
   // second pass (twice the capacity, edge table still in LDS) for the cells
@@ -1857,7 +1859,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
       k_clip<SPL_MID, PM_MID, 1><<<nbig, 64, 0, s>>>(used.sp, used.sidx, used.n, used.lo, used.hi, used.lv, bmin, bmax,
                                                     prm.radius, klist.p, nullptr, faces_big.p, bigslot.p, counts.p,
                                                     sc->nrast, sc->cull, sc->flags, warm_row, warm_col, warm_tri, warm_wit,
-                                                    sp.p, spos.p, n, sc->wit, prm.normal, prm.tex, sc->ball);
+                                                    sp.p, spos.p, n, sc->wit, prm.normal, prm.tex, sc->ball, sc->ball_top);
     }
     PF_HIP_TRY(hipGetLastError());
     unsigned int nbig3 = 0;
@@ -1869,7 +1871,7 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
       k_clip<SPL_BIG, PM_BIG, 2><<<nbig3, 64, 0, s>>>(used.sp, used.sidx, used.n, used.lo, used.hi, used.lv, bmin, bmax,
                                                      prm.radius, klist.p, eo_big.p, faces_big.p, bigslot.p, counts.p,
                                                      sc->nrast, sc->cull, sc->flags, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                     nullptr, 0, sc->wit, prm.normal, prm.tex, sc->ball);
+                                                     nullptr, 0, sc->wit, prm.normal, prm.tex, sc->ball, sc->ball_top);
       PF_HIP_TRY(hipGetLastError());
     }
   }

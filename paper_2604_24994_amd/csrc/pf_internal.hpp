@@ -49,6 +49,7 @@ struct Scene {
                                    // non-empty bounded cell; < 0: hidden
   float4* ball = nullptr;          // centre and radius of a ball around the dense part of the
                                    // bounded cell; radius < 0: none (never rendered)
+  float* ball_top = nullptr;       // largest displacement of the face that the ball allows (live_ball)
   int32_t* flags = nullptr;
   int32_t* wit = nullptr;          // [n][8] per empty cell: planes that prove it empty, recent planes (pf_build.hip)
   // adjacency, CSR; per cell: raster faces, other neighbour faces, box faces
@@ -105,6 +106,41 @@ struct RecBuf {
   int64_t cap = 0;                    // record capacity
   int64_t seg_cap = 0;                // segment capacity
 };
+
+// What a detail site (s, d) = t[0..2] may move the face by: d, without bound
+// where it is not finite (its weights are no convex combination then).
+__device__ inline float site_top(const float* __restrict__ t) {
+  return fabsf(t[0]) + fabsf(t[1]) + fabsf(t[2]) < INFINITY ? t[2] : INFINITY;
+}
+
+// A ball given by the build, of cell-local radius r around (x, y, z): widened by
+// what the centre's rounding and the pieces' float32 ends can be off, far being
+// the site's distance from the origin (sum of magnitudes).
+__device__ inline float4 widened_ball(float x, float y, float z, float r, double far) {
+  return make_float4(x, y, z, r * (1.0f + 1e-4f) + (float)(1e-6 * far));
+}
+
+// The cell's ball for the texture as it is now.  The build's covers the dense
+// part while no site lifts the face above ball_top; the texture is the caller's
+// and a render reads it live, so where one does, the ball is that of the whole
+// bounded cell (its centre p and its cull radius).
+__device__ inline float4 live_ball(const float4* __restrict__ geo, const float* __restrict__ cull,
+                                   const float4* __restrict__ ball, const float* __restrict__ ball_top,
+                                   const float* __restrict__ tex, int64_t i, bool& grown) {
+  grown = false;
+  const float r = cull[i];
+  if (!(r >= 0.0f)) return make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+  const float4 b = ball[i];
+  const float top = ball_top[i];
+  if (!(top < INFINITY)) return b;
+  float now = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < KD; ++k) now = fmaxf(now, site_top(tex + (i * KD + k) * TEXW));
+  if (!(now > top)) return b;
+  grown = true;
+  const float4 g = geo[i];
+  return widened_ball(g.x, g.y, g.z, r, fabs((double)g.x) + fabs((double)g.y) + fabs((double)g.z));
+}
 
 // Thread-local error text.
 void set_error(const std::string& msg);

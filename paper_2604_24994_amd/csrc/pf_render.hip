@@ -208,22 +208,47 @@ __device__ inline int cell_rect(const ViewArgs& v, const float4 g, int& x0, int&
   return 1;
 }
 
+// What live_ball takes.
+struct BallArgs {
+  const float4* geo;
+  const float* cull;
+  float4* ball;
+  const float* ball_top;
+  const float* tex;
+};
+
+// The cells' balls for a group of several views (live_ball).
+__global__ void k_live_ball(BallArgs b, int64_t n, float4* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool grown;
+  if (i < n) out[i] = live_ball(b.geo, b.cull, b.ball, b.ball_top, b.tex, i, grown);
+}
+
 // blockIdx.y = view; one thread per (view, cell).
 // Cells whose footprint needs the per-tile cone test are listed in
 // cone_list (as view * n + cell) and counted by k_cone_count.
-__global__ void k_view_count(const ViewDev* __restrict__ views, const float4* __restrict__ geo,
-                             const float4* __restrict__ ball, const float* __restrict__ power, int64_t n,
-                             uint32_t* __restrict__ cnt, uint32_t* __restrict__ key, uint32_t* __restrict__ cone_list,
+// LIVE (one view): the balls are formed here; else k_live_ball did.
+template <bool LIVE>
+__global__ void k_view_count(const ViewDev* __restrict__ views, BallArgs b, float4* __restrict__ live,
+                             const float* __restrict__ power, int64_t n, uint32_t* __restrict__ cnt,
+                             uint32_t* __restrict__ key, uint32_t* __restrict__ cone_list,
                              uint32_t* __restrict__ cone_n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const ViewArgs& v = views[blockIdx.y].v;
   const int64_t o = (int64_t)blockIdx.y * n + i;
-  const float4 g = geo[i];
+  const float4 g = b.geo[i];
   int x0, x1, y0, y1;
   Cone k;
   uint32_t c = 0;
-  const int mode = cell_rect(v, ball[i], x0, x1, y0, y1, k);
+  float4 bl;
+  if constexpr (LIVE) {
+    bool grown;
+    bl = live[i] = live_ball(b.geo, b.cull, b.ball, b.ball_top, b.tex, i, grown);
+  } else {
+    bl = live[i];
+  }
+  const int mode = cell_rect(v, bl, x0, x1, y0, y1, k);
   if (o == 0) cnt[(int64_t)gridDim.y * n] = 0;   // (the scan's last entry)
   if (mode == 1) {
     c = (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
@@ -1282,9 +1307,13 @@ __global__ void __launch_bounds__(256) k_seg_total(const int4* __restrict__ seg,
 
 // argmin over cells with a non-empty power cell of pow(o, p_i) in float64;
 // ties go to the lower index.  Stage 1: per block; stage 2: one block.
+// On the way, the balls that the texture has outgrown since the build are
+// replaced in place (live_ball): a ball that covers the whole bounded cell stays
+// right whatever the texture becomes, and passes of several streams that find
+// one outgrown all write the same value.
 __global__ void __launch_bounds__(256) k_start_partial(const float* __restrict__ p, const float* __restrict__ w,
                                                        const int32_t* __restrict__ flags, int64_t n, double ox,
-                                                       double oy, double oz, double* __restrict__ pk,
+                                                       double oy, double oz, BallArgs b, double* __restrict__ pk,
                                                        long long* __restrict__ pi) {
   double best = INFINITY;
   long long bi = -1;
@@ -1296,6 +1325,9 @@ __global__ void __launch_bounds__(256) k_start_partial(const float* __restrict__
       best = k;
       bi = i;
     }
+    bool grown;
+    const float4 bl = live_ball(b.geo, b.cull, b.ball, b.ball_top, b.tex, i, grown);
+    if (grown) b.ball[i] = bl;
   }
   __shared__ double sk[256];
   __shared__ long long si[256];
@@ -1650,11 +1682,13 @@ k_trace(ViewArgs v, int64_t tile_first, SceneDev S, const int32_t* __restrict__ 
   }
 }
 
-SceneDev scene_dev(const Scene& sc) {
+BallArgs ball_args(const Scene& sc) { return {sc.geo, sc.cull, sc.ball, sc.ball_top, sc.prm.tex}; }
+
+SceneDev scene_dev(const Scene& sc, const float4* ball) {
   SceneDev d;
   d.geo = sc.geo;
   d.nrm = sc.nrm;
-  d.ball = sc.ball;
+  d.ball = ball;
   d.row = sc.row;
   d.nrast = sc.nrast;
   d.col = sc.col;
@@ -1719,9 +1753,12 @@ struct Arena {
 // its kernels).  The arrays that start as zeros are neighbours.
 struct GroupLayout {
   Arena fixed, pairs;
-  int64_t views, cnt, key, off, cone_list, plan, toff, zero, tcnt, fill, cone_n, long_n, zero_end, ptile, pval, sorted, long_list;
-  GroupLayout(int64_t nvc, int nv, int64_t ntiles, int64_t np) {
+  int64_t views, ball, cnt, key, off, cone_list, plan, toff, zero, tcnt, fill, cone_n, long_n, zero_end, ptile, pval,
+      sorted, long_list;
+  GroupLayout(int64_t n, int nv, int64_t ntiles, int64_t np) {
+    const int64_t nvc = (int64_t)nv * n;
     views = fixed.add(nv, sizeof(ViewDev));
+    ball = fixed.add(n, sizeof(float4));
     cnt = fixed.add(nvc + 1, 4);
     key = fixed.add(nvc, 4);
     off = fixed.add(nvc + 1, 4);
@@ -1744,7 +1781,7 @@ struct GroupLayout {
 
 int64_t raster_group_bytes(int64_t n, int nv, int64_t ntiles, int64_t np) {
   const int64_t nvc = (int64_t)nv * n;
-  const GroupLayout l(nvc, nv, ntiles, np);
+  const GroupLayout l(n, nv, ntiles, np);
   return l.fixed.bytes + l.pairs.bytes + scan_scratch_bytes(nvc + 1) + scan_scratch_bytes(ntiles + 1);
 }
 
@@ -1762,6 +1799,7 @@ struct Group {
     T* p = nullptr;
   };
   Part<ViewDev> views;
+  Part<float4> ball;
   Part<uint32_t> cnt, key, off, tcnt, toff, fill, cone_list, cone_n, long_n, ptile, plan, long_list;
   Part<unsigned long long> pval, sorted;
   explicit Group(hipStream_t s) : fixed(s), pairs(s) {}
@@ -1789,10 +1827,11 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   G.ntiles = ntiles;
   const int64_t nvc = (int64_t)nv * n;
   {
-    const GroupLayout l(nvc, nv, ntiles, 0);
+    const GroupLayout l(n, nv, ntiles, 0);
     PF_HIP_TRY(G.fixed.alloc(l.fixed.bytes));
     char* p = G.fixed.p;
     G.views.p = (ViewDev*)(p + l.views);
+    G.ball.p = (float4*)(p + l.ball);
     G.cnt.p = (uint32_t*)(p + l.cnt);
     G.key.p = (uint32_t*)(p + l.key);
     G.off.p = (uint32_t*)(p + l.off);
@@ -1808,9 +1847,19 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   PF_HIP_TRY(hipMemcpyAsync(G.views.p, hv.data(), sizeof(ViewDev) * nv, hipMemcpyHostToDevice, s));
   const dim3 g((unsigned)((n + 255) / 256), (unsigned)nv);
   {
+    // one view's threads form its balls themselves (for 256x256 at 1,048,576
+    // cells 48 us in one launch, 25 and 35 in two); with more views each ball
+    // is formed once
     ProfScope ps("k_view_count", s);
-    k_view_count<<<g, 256, 0, s>>>(G.views.p, sc.geo, sc.ball, sc.prm.power, n, G.cnt.p, G.key.p, G.cone_list.p,
-                                   G.cone_n.p);
+    if (nv == 1) {
+      k_view_count<true><<<g, 256, 0, s>>>(G.views.p, ball_args(sc), G.ball.p, sc.prm.power, n, G.cnt.p, G.key.p,
+                                           G.cone_list.p, G.cone_n.p);
+    } else {
+      k_live_ball<<<g.x, 256, 0, s>>>(ball_args(sc), n, G.ball.p);
+      PF_HIP_TRY(hipGetLastError());
+      k_view_count<false><<<g, 256, 0, s>>>(G.views.p, ball_args(sc), G.ball.p, sc.prm.power, n, G.cnt.p, G.key.p,
+                                            G.cone_list.p, G.cone_n.p);
+    }
   }
   PF_HIP_TRY(hipGetLastError());
   // A workgroup per cell that could be listed where those that find nothing
@@ -1822,7 +1871,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
     PF_HIP_TRY(hipStreamSynchronize(s));
   }
   if (gcone) {
-    k_cone_count<<<gcone, 256, 0, s>>>(G.views.p, sc.ball, n, G.cone_list.p, G.cone_n.p, G.cnt.p);
+    k_cone_count<<<gcone, 256, 0, s>>>(G.views.p, G.ball.p, n, G.cone_list.p, G.cone_n.p, G.cnt.p);
     PF_HIP_TRY(hipGetLastError());
   }
   PF_HIP_TRY(exclusive_scan_u32(G.cnt.p, G.off.p, nvc + 1, nullptr, s));
@@ -1834,7 +1883,7 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   __atomic_store(&sc.pairs_per_cell, &ppc, __ATOMIC_RELAXED);
   if (count_only) return PF_OK;
   {
-    const GroupLayout l(nvc, nv, ntiles, np);
+    const GroupLayout l(n, nv, ntiles, np);
     PF_HIP_TRY(G.pairs.alloc(l.pairs.bytes));
     G.ptile.p = (uint32_t*)(G.pairs.p + l.ptile);
     G.pval.p = (unsigned long long*)(G.pairs.p + l.pval);
@@ -1843,9 +1892,9 @@ pf_status bin_group(Scene& sc, const pf_camera* cams, Group& G, hipStream_t s, b
   }
   {
     ProfScope ps("k_view_emit", s);
-    k_view_emit<<<g, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.ptile.p, G.pval.p, G.tcnt.p);
+    k_view_emit<<<g, 256, 0, s>>>(G.views.p, G.ball.p, n, G.off.p, G.key.p, G.ptile.p, G.pval.p, G.tcnt.p);
     if (gcone)
-      k_cone_emit<<<gcone, 256, 0, s>>>(G.views.p, sc.ball, n, G.off.p, G.key.p, G.cone_list.p, G.cone_n.p,
+      k_cone_emit<<<gcone, 256, 0, s>>>(G.views.p, G.ball.p, n, G.off.p, G.key.p, G.cone_list.p, G.cone_n.p,
                                         G.ptile.p, G.pval.p, G.tcnt.p);
   }
   PF_HIP_TRY(hipGetLastError());
@@ -1872,10 +1921,10 @@ void launch_raster(Scene& sc, Group& G, float t_min, float* rgba, hipStream_t s,
   k_split_plan<<<1, PLAN_THREADS, 0, s>>>(G.toff.p, first, count, G.plan.p);
   // (one workgroup of sixteen waves per CU is resident)
   k_raster_split<STORE, COUNT><<<(unsigned)std::min<int64_t>(4 * count, 256), 64 * NW, 0, s>>>(
-      G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
+      G.views.p, G.nv, scene_dev(sc, G.ball.p), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
       rb.seg, rb.wtail, wtail_base, rb.cap, rb.seg_cap, first, G.plan.p, counters);
   k_raster<STORE, COUNT><<<(unsigned)count, 256, 0, s>>>(
-      G.views.p, G.nv, scene_dev(sc), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
+      G.views.p, G.nv, scene_dev(sc, G.ball.p), G.sorted.p, G.toff.p, t_min, rgba, rb.ri, rb.rf, rb.rt, rb.head, rb.counter,
       rb.seg, rb.wtail, wtail_base, rb.cap, rb.seg_cap, first, G.plan.p, counters);
 }
 
@@ -1981,7 +2030,7 @@ pf_status trace_view(const Scene& sc, const pf_camera& cam, float t_min, int max
     start = start_own.p;
   }
   k_start_partial<<<nb, 256, 0, s>>>(sc.prm.p, sc.prm.power, sc.flags, n, cam.c2w[3], cam.c2w[7], cam.c2w[11],
-                                     pk, pi);
+                                     ball_args(sc), pk, pi);
   PF_HIP_TRY(hipGetLastError());
   k_start_final<<<1, 256, 0, s>>>(pk, pi, nb, start);
   PF_HIP_TRY(hipGetLastError());
@@ -1989,21 +2038,21 @@ pf_status trace_view(const Scene& sc, const pf_camera& cam, float t_min, int max
   if (rec) {
     const RecBuf& rb = *rec;
     if (counters)
-      k_trace<true, true><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc), start, t_min, max_steps,
+      k_trace<true, true><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc, sc.ball), start, t_min, max_steps,
                                                            rgba, trunc_dev, view, rb.ri, rb.rf, rb.rt,
                                                            rb.head + pix_base, rb.counter, rb.seg, rb.cap, rb.seg_cap,
                                                            counters);
     else
-      k_trace<true, false><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc), start, t_min, max_steps,
+      k_trace<true, false><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc, sc.ball), start, t_min, max_steps,
                                                             rgba, trunc_dev, view, rb.ri, rb.rf, rb.rt,
                                                             rb.head + pix_base, rb.counter, rb.seg, rb.cap,
                                                             rb.seg_cap, nullptr);
   } else if (counters) {
-    k_trace<false, true><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc), start, t_min, max_steps, rgba,
+    k_trace<false, true><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc, sc.ball), start, t_min, max_steps, rgba,
                                                           trunc_dev, 0, nullptr, nullptr, nullptr, nullptr, nullptr,
                                                           nullptr, 0, 0, counters);
   } else {
-    k_trace<false, false><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc), start, t_min, max_steps,
+    k_trace<false, false><<<(unsigned)ntiles, 256, 0, s>>>(v, tile_first, scene_dev(sc, sc.ball), start, t_min, max_steps,
                                                            rgba, trunc_dev, 0, nullptr, nullptr, nullptr, nullptr,
                                                            nullptr, nullptr, 0, 0, nullptr);
   }
