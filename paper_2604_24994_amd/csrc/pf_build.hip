@@ -737,10 +737,14 @@ __device__ float4 dense_ball(const Shared<SPL, PM>& S, const EOT* eo, const Poly
                              const float* __restrict__ normal, float disp, float r) {
   constexpr int NT = 64 * SPL;
   const int lane = threadIdx.x;
-  const double ax = normal[0], ay = normal[1], az = normal[2];
+  // (a normal whose float32 unit vector (k_prep) is not finite cuts nothing off:
+  // every comparison of the piece with its face is false)
+  const float fx = normal[0], fy = normal[1], fz = normal[2], finv = 1.0f / sqrtf(fx * fx + fy * fy + fz * fz);
+  const bool face = fabsf(fx * finv) + fabsf(fy * finv) + fabsf(fz * finv) < INFINITY;
+  const double ax = fx, ay = fy, az = fz;
   const double inv = 1.0 / sqrt(ax * ax + ay * ay + az * az);
-  const double nx = ax * inv, ny = ay * inv, nz = az * inv;
-  const double top = (double)disp * (1.0 + 1e-5) + 1e-7 * (double)r;
+  const double nx = face ? ax * inv : 0.0, ny = face ? ay * inv : 0.0, nz = face ? az * inv : 0.0;
+  const double top = face ? (double)disp * (1.0 + 1e-5) + 1e-7 * (double)r : INFINITY;
   uint64_t above[SPL];
 #pragma unroll
   for (int s = 0; s < SPL; ++s) {

@@ -2,8 +2,8 @@
 
 The ball is formed by the build from the faces' largest displacements, while
 every render reads the texture as it is then.  Displacements far beyond the
-cell, to either side, and displacements raised in place after the build, each
-against the float64 oracle or a fresh build.
+cell, to either side, displacements raised in place after the build, and
+normals without a direction, each against the float64 oracle or a fresh build.
 
 Bars: 1e-4 per pixel against the oracle, as everywhere; 1e-6 against a fresh
 build (the same pieces in the same order)."""
@@ -127,3 +127,29 @@ def test_displacements_raised_in_place_walk_alone():
         assert float((got.reshape(-1) - want.reshape(-1)).abs().max()) <= 1e-6, noalloc
         scene.destroy()
         fresh.destroy()
+
+@pytest.mark.parametrize("kind", ["zero", "nan", "inf", "tiny"])
+def test_normal_without_direction_leaves_the_cell_dense(kind):
+    # Without a direction no face cuts the cell: all of it is dense, and its
+    # sites weigh alike (given one texture here, so that no weights matter).
+    # The reference has a face moved out of the cell instead.
+    import paper_2604_24994_amd as pf
+    print(f"case normal {kind}", flush=True)
+    sc, cam = _scene()
+    sc.tex = np.array(sc.tex)
+    sc.tex[:, :, 3:] = sc.tex[:, :1, 3:]
+    cells = np.arange(0, sc.n, 7)
+    ref_sc = sc.copy()
+    ref_sc.tex = np.array(ref_sc.tex)
+    ref_sc.tex[cells, :, 2] = 10.0
+    ref = oracle.render_painter(ref_sc, cam).reshape(cam.height, cam.width, 4)
+    assert np.abs(oracle.render_painter(sc, cam).reshape(ref.shape) - ref).max() > 1e-2
+    sc.normal = np.array(sc.normal)
+    sc.normal[cells] = {"zero": 0.0, "nan": np.nan, "inf": np.inf, "tiny": 0.0}[kind]
+    if kind == "tiny":
+        sc.normal[cells, 1] = 1e-30   # its length is 0 in float32
+    scene = pf.build_scene(sc, box=_box(cam))
+    for name, img in _images(pf, scene, cam).items():
+        print(f"  {name} {np.abs(img - ref).max():.2e}")
+        assert np.abs(img - ref).max() <= 1e-4, name
+    scene.destroy()
