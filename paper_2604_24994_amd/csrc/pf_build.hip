@@ -1379,9 +1379,14 @@ __global__ void __launch_bounds__(64) k_connect(const float4* __restrict__ sp, c
 // leave nothing of them: a lane per cell.  With the four planes (m, h) in the
 // cell's frame, weights l >= 0 on the last three with m_0 + sum l m = 0 and
 // h_0 + sum l h < 0 prove that no x has m.x <= h for all four, so the power
-// cell is empty whatever the other sites are; the comparison keeps a margin
-// far above the rounding of the sums, and a cell that misses it is clipped
-// like any other.  keep[k] (sorted position) says which cells are left; for
+// cell is empty whatever the other sites are.  The weights are rounded, and
+// where the normals are nearly coplanar little of them is left (sites moved
+// into one plane: det is what a fused multiply-add leaves of zero), so the
+// proof is made for the weights as they are: with e = m_0 + sum l m, every x of
+// the cell has e.x <= h_0 + sum l h, and within the domain box e.x is at least
+// -(|e_x| X + |e_y| Y + |e_z| Z).  Below that, less the rounding of e and of the
+// offsets h and a margin, nothing is left whatever the l are; a cell that misses
+// it is clipped like any other.  keep[k] (sorted position) says which cells are left; for
 // the others the outputs of an empty cell are written.
 __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, const int32_t* __restrict__ sidx,
                                                  const int32_t* __restrict__ spos, int64_t n, float3 bmin, float3 bmax,
@@ -1399,14 +1404,17 @@ __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, 
     const float4 me = sp[k];
     const double px = me.x, py = me.y, pz = me.z, wi = me.w;
     bool ok = wi > -INFINITY;
-    auto plane = [&](int v, double& mx, double& my, double& mz) -> double {
-      mx = my = mz = 0.0;
+    // offset h of plane v; H: the magnitudes it is formed from
+    auto plane = [&](int v, double& mx, double& my, double& mz, double& H) -> double {
+      mx = my = mz = H = 0.0;
       if (v >= 0 && v < n && v != self) {
         const float4 q = sp[spos[v]];
         mx = (double)q.x - px;
         my = (double)q.y - py;
         mz = (double)q.z - pz;
-        return 0.5 * (mx * mx + my * my + mz * mz + wi - (double)q.w);
+        const double mm = mx * mx + my * my + mz * mz;
+        H = mm + fabs(wi) + fabs((double)q.w);
+        return 0.5 * (mm + wi - (double)q.w);
       }
       if (v <= -2 && v >= -7) {
         const int f = -2 - v, ax = f >> 1;
@@ -1416,18 +1424,20 @@ __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, 
         mz = ax == 2 ? sgn : 0.0;
         const double lim = (f & 1) ? (ax == 0 ? bmin.x : ax == 1 ? bmin.y : bmin.z)
                                    : (ax == 0 ? bmax.x : ax == 1 ? bmax.y : bmax.z);
-        return sgn * (lim - (ax == 0 ? px : ax == 1 ? py : pz));
+        const double at = ax == 0 ? px : ax == 1 ? py : pz;
+        H = fabs(lim) + fabs(at);
+        return sgn * (lim - at);
       }
       ok = false;
       return 0.0;
     };
-    double x0, y0, z0;
-    const double h0 = plane(w0.x, x0, y0, z0);
+    double x0, y0, z0, H0;
+    const double h0 = plane(w0.x, x0, y0, z0, H0);
     if (ok && x0 == 0.0 && y0 == 0.0 && z0 == 0.0) {
       gone = h0 < 0.0 || (h0 == 0.0 && w0.x < self);   // coincident sites
     } else if (ok) {
-      double xa, ya, za, xb, yb, zb, xc, yc, zc;
-      const double ha = plane(w0.y, xa, ya, za), hb = plane(w0.z, xb, yb, zb), hc = plane(w0.w, xc, yc, zc);
+      double xa, ya, za, xb, yb, zb, xc, yc, zc, Ha, Hb, Hc;
+      const double ha = plane(w0.y, xa, ya, za, Ha), hb = plane(w0.z, xb, yb, zb, Hb), hc = plane(w0.w, xc, yc, zc, Hc);
       // (cross products of the pairs, determinant, weights by Cramer's rule)
       const double bcx = yb * zc - zb * yc, bcy = zb * xc - xb * zc, bcz = xb * yc - yb * xc;
       const double cax = yc * za - zc * ya, cay = zc * xa - xc * za, caz = xc * ya - yc * xa;
@@ -1439,7 +1449,16 @@ __global__ void __launch_bounds__(256) k_witness(const float4* __restrict__ sp, 
                      lc = (x0 * abx + y0 * aby + z0 * abz) * inv;
         const double v = h0 + la * ha + lb * hb + lc * hc;
         const double scale = fabs(h0) + fabs(la * ha) + fabs(lb * hb) + fabs(lc * hc);
-        gone = la >= 0.0 && lb >= 0.0 && lc >= 0.0 && v < -1e-8 * scale;
+        // e, and the rounding of its sums and of the h (a few units of 1.1e-16)
+        auto left = [&](double m0, double ma, double mb, double mc) {
+          return fabs(m0 + la * ma + lb * mb + lc * mc) +
+                 1e-15 * (fabs(m0) + fabs(la * ma) + fabs(lb * mb) + fabs(lc * mc));
+        };
+        const double reach = left(x0, xa, xb, xc) * fmax(fabs((double)bmin.x - px), fabs((double)bmax.x - px)) +
+                             left(y0, ya, yb, yc) * fmax(fabs((double)bmin.y - py), fabs((double)bmax.y - py)) +
+                             left(z0, za, zb, zc) * fmax(fabs((double)bmin.z - pz), fabs((double)bmax.z - pz));
+        const double round_h = 1e-15 * (H0 + la * Ha + lb * Hb + lc * Hc);
+        gone = la >= 0.0 && lb >= 0.0 && lc >= 0.0 && v < -(1e-8 * scale + reach + round_h);
       }
     }
   }
