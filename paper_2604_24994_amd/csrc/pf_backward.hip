@@ -45,8 +45,17 @@ namespace {
 
 constexpr int BWD_THREADS = 64;     // one wave per workgroup
 constexpr int CHUNK = 2048;         // records per workgroup
-constexpr int FMAX_B = 64;          // faces held in LDS (planes and sums); faces beyond go to global memory directly
-constexpr int CAM_B = 8;            // cameras held in LDS (with more, every record reads its own from global memory)
+// LDS rows for a cell's raster faces: planes and sums of up to FMAX_B faces, or,
+// for a cell with more, the sums of the first 2 FMAX_B (its planes are read per
+// record, and the sums of faces beyond go to global memory batch by batch).  The
+// LDS of eight workgroups per CU has no room for more: 20,264 of 20,480 bytes.
+// 26 M records of 512 cells with 120 faces take 3.0 ms (9.0 with the faces from 64
+// on added to global memory record by record), 28 M with 140 faces 3.2 (6.0).
+constexpr int FMAX_B = 64;
+// Cameras held in LDS; with more, every record reads its own from global memory.
+// (Ten would fit beside the rest; of 262,144 cells in 8, 9 and 16 views of 640x360
+// the kernel takes 0.149, 0.144 and 0.129 ms per million records.)
+constexpr int CAM_B = 8;
 constexpr int NCELL = 12;           // p(3) w r n(3) lambda rgb(3)
 constexpr int NSUM = NCELL + 3 * KD;  // + detail-site s(2), d per site
 constexpr int CPAD = 68;             // row pitch of the transposed phase's LDS tables: 16-byte rows, banks spread
@@ -277,14 +286,16 @@ constexpr int ACC_ROWS = ACC_D + KD / 4;
 static_assert(NCELL % 4 == 0 && KD % 4 == 0, "the sums go four to a row");
 typedef float4 AccRow[64];
 
-// facc[f] += (x, y, z, w) for the lanes with f >= 0, face by face: a chunk's
-// records are neighbouring pixels of one cell, so a wave holds few faces, and
+// add(f, c, sum of component c of (x, y, z, w)) for every f >= 0 that lanes
+// hold, c = 0..3 in one lane each, face by face: a chunk's records are
+// neighbouring pixels of one cell, so a wave holds few faces, and
 // LDS atomics, which the LDS takes about one lane at a time, cost more than a
 // reduction per face (4.5 of k_bwd_cell's 36 ms).  In the reduction permlane32
 // swaps pair x with y and z with w, a permlane16 swap pairs the results, so that
 // after two adds rows 0..3 of the wave hold partial sums of x, z, y, w; four DPP
 // steps finish the row sums.  All lanes take part.
-__device__ inline void face_sums(float (*facc)[4], int f, float x, float y, float z, float w) {
+template <typename Add>
+__device__ inline void face_sums(int f, float x, float y, float z, float w, Add&& add) {
   const int lane = threadIdx.x;
   const int comp = ((lane >> 4) & 1) * 2 + (lane >> 5);
   for (uint64_t m = __ballot(f >= 0); m;) {
@@ -302,7 +313,7 @@ __device__ inline void face_sums(float (*facc)[4], int f, float x, float y, floa
     t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x4E, 0xf, 0xf, false));  // quad [2,3,0,1]
     t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x141, 0xf, 0xf, false)); // row half mirror
     t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x140, 0xf, 0xf, false)); // row mirror
-    if ((lane & 15) == 0) atomicAdd(&facc[g][comp], t);
+    if ((lane & 15) == 0) add(g, comp, t);
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -428,8 +439,8 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
   __shared__ __align__(16) float st_gw[KD][CPAD];   // the same of minus dL/dw_k
   __shared__ AccRow acc[ACC_ROWS];       // per-lane sums over the chunk's batches
   float ta_sum = 0.0f;                   // the same of the contribution
-  __shared__ float facc[FMAX_B][4];      // per face: dL/dm, dL/dw_j
-  __shared__ float4 s_pl[FMAX_B];        // the cell's raster faces
+  __shared__ __align__(16) float facc[2 * FMAX_B][4];   // per face: dL/dm, dL/dw_j; from FMAX_B on its plane or more sums
+  float4* s_pl = reinterpret_cast<float4*>(facc + FMAX_B);
   __shared__ pf_camera s_cam[CAM_B];
   __shared__ double s_iw[CAM_B];         // 1 / width
   __shared__ double s_fr[12];            // the cell's face frame (wave-uniform)
@@ -446,7 +457,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
   const int lane = threadIdx.x;
   const int r0 = row[ci];
   const int nf = nrast[ci];
-  const int nfl = min(nf, FMAX_B);
+  const int nfl = min(nf, 2 * FMAX_B);   // faces summed in LDS
   const float* __restrict__ txc = tex + (int64_t)ci * KD * TEXW;
   for (int t = 0; t < ACC_ROWS; ++t) acc[t][lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (lane < 2) s_zero[lane] = 0;
@@ -459,11 +470,10 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int c = 0; c < 3; ++c) site0[3 * k + c] = txc[k * TEXW + c];
   }
-  static_assert(FMAX_B <= BWD_THREADS, "a face per lane");
-  if (lane < nfl) {
-    s_pl[lane] = plane[r0 + lane];
-    for (int c = 0; c < 4; ++c) facc[lane][c] = 0.0f;
-  }
+  static_assert(FMAX_B <= BWD_THREADS, "a plane per lane");
+  for (int f = lane; f < nfl; f += BWD_THREADS)
+    for (int c = 0; c < 4; ++c) facc[f][c] = 0.0f;
+  if (nf <= FMAX_B && lane < nf) s_pl[lane] = plane[r0 + lane];
   if (ncam <= CAM_B) {
     if (lane < ncam) s_iw[lane] = 1.0 / (double)cams[lane].width;
     static_assert(sizeof(pf_camera) % 4 == 0, "copied by words");
@@ -552,9 +562,9 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     // the binding faces' planes and the camera, from LDS where they fit
     const bool on0 = b0 >= 0 && b0 < nf, on1 = b1 >= 0 && b1 < nf;
     float4 pl0 = s_pl[min(max(b0, 0), FMAX_B - 1)], pl1 = s_pl[min(max(b1, 0), FMAX_B - 1)];
-    if (nf > FMAX_B) {
-      if (on0 && b0 >= FMAX_B) pl0 = plane[r0 + b0];
-      if (on1 && b1 >= FMAX_B) pl1 = plane[r0 + b1];
+    if (nf > FMAX_B) {   // (what was read there are sums)
+      if (on0) pl0 = plane[r0 + b0];
+      if (on1) pl1 = plane[r0 + b1];
     }
     pl0 = on0 ? pl0 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     pl1 = on1 ? pl1 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -788,7 +798,7 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
     // ---------------- ends of the bounded interval
     float g_beta = 0.0f, g_r = 0.0f, g_wi = 0.0f;
     float gpx = 0.0f, gpy = 0.0f, gpz = 0.0f;   // explicit p_i terms (planes)
-    // (returns what the binding face's plane gets, for the sums in LDS; face -1: none)
+    // (returns what the binding face's plane gets, face -1: none)
     struct FaceGrad {
       int f;
       float x, y, z, w;
@@ -821,32 +831,31 @@ __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_e
         gpy -= gmy;
         gpz -= gmz;
         g_wi += 0.5f * gh;
-        if (b < FMAX_B) {
-          fg.f = b;
-          fg.x = gmx;
-          fg.y = gmy;
-          fg.z = gmz;
-          fg.w = -0.5f * gh;
-        } else {
-          const int j = col[r0 + b];
-          if (j >= 0) {
-            if (G.p) {
-              atomicAdd(G.p + 3 * (int64_t)j, gmx);
-              atomicAdd(G.p + 3 * (int64_t)j + 1, gmy);
-              atomicAdd(G.p + 3 * (int64_t)j + 2, gmz);
-            }
-            if (G.power) atomicAdd(G.power + j, -0.5f * gh);
-          }
-        }
+        fg.f = b;
+        fg.x = gmx;
+        fg.y = gmy;
+        fg.z = gmz;
+        fg.w = -0.5f * gh;
       }
       return fg;
     };
-    {
-      const FaceGrad e0 = end_grad(b0, pl0, s0, a0, valid ? g_s0 : 0.0f, false);
-      face_sums(facc, e0.f, e0.x, e0.y, e0.z, e0.w);
-      const FaceGrad e1 = end_grad(b1, pl1, s1, a1, valid ? g_s1 : 0.0f, true);
-      face_sums(facc, e1.f, e1.x, e1.y, e1.z, e1.w);
-    }
+    auto sum_faces = [&](const FaceGrad& e) {
+      if (__builtin_expect(nf <= 2 * FMAX_B, 1)) {
+        face_sums(e.f, e.x, e.y, e.z, e.w, [&](int g, int c, float t) { atomicAdd(&facc[g][c], t); });
+      } else {
+        face_sums(e.f, e.x, e.y, e.z, e.w, [&](int g, int c, float t) {
+          if (g < 2 * FMAX_B) {
+            atomicAdd(&facc[g][c], t);
+            return;
+          }
+          const int j = col[r0 + g];
+          float* d = c < 3 ? (G.p ? G.p + 3 * (int64_t)j + c : nullptr) : (G.power ? G.power + j : nullptr);
+          if (j >= 0 && d) atomicAdd(d, t);
+        });
+      }
+    };
+    sum_faces(end_grad(b0, pl0, s0, a0, valid ? g_s0 : 0.0f, false));
+    sum_faces(end_grad(b1, pl1, s1, a1, valid ? g_s1 : 0.0f, true));
     // q = oc - beta d, beta = oc.d, oc = o - p_i
     const float gqd = gqx * fx + gqy * fy + gqz * fz;
     gpx += -(gqx - gqd * fx) - g_beta * fx;
