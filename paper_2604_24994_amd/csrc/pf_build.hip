@@ -37,7 +37,7 @@ constexpr int SPL_BIG = 8;        // vertex slots per lane of the third pass
 // (levels - 2) x 63 + 64 + the root's children: 190 entries at 16M sites
 constexpr int STACK = 192;
 constexpr int WIT = 8;           // per empty cell: sites whose planes emptied it (seeds of the next build)
-constexpr int64_t ELIM_MIN = 16384;   // cells from which the empty ones are taken out first (build_scene_impl)
+constexpr int64_t ELIM_MIN = 24000;   // cells from which the empty ones are taken out first (build_scene_impl)
 constexpr int RING_K = 16;        // rank of the leaf mate that sets the first ring radius
 // Upper bound on candidate clips plus node visits per cell; a cell that
 // reaches it is reported as over capacity instead of running on.
@@ -1804,7 +1804,11 @@ pf_status build_scene_impl(const pf_params& prm, const pf_build_opts& opt, hipSt
   // the same without it, and most sites can be empty: 70% at 1,048,576 cells,
   // where k_clip took 19.9 ms with them and 12.7 without (k_witness 0.12).
   // Below ELIM_MIN cells the extra launches and the count read back cost more
-  // than they save.  (Without a previous build, clipping each cell against its
+  // than they save: pf_update_scene after moves of 1e-4 takes, with and without,
+  // 0.92 and 0.84 ms at 16,384 cells uniform in a cube (1.06 and 0.99 in the
+  // mixture of surfaces), 1.05 and 1.00 (1.23 and 1.25) at 24,000, 1.13 and 1.13
+  // (1.95 and 2.13) at 32,768, 1.34 and 1.54 (2.40 and 2.97) at 65,536.
+  // (Without a previous build, clipping each cell against its
   // own leaf first finds too few of them: 7.1 ms to shorten 14.6 by 1.8 at
   // 300,000 cells.)
   struct Part {

@@ -26,8 +26,8 @@ MOVES = {
 @pytest.mark.parametrize("seed", [4, 5])
 def test_rebuild_equals_fresh_build(name, seed):
     import paper_2604_24994_amd as pf
-    print(f"case 20,000 cells to {name}, seed {seed}", flush=True)
-    params = pf.to_device_params(W.scene_mixture(20000, seed=seed))
+    print(f"case 30,000 cells to {name}, seed {seed}", flush=True)
+    params = pf.to_device_params(W.scene_mixture(30000, seed=seed))
     scene = pf.build_scene(params)
     moved = dict(params)
     moved["p"] = MOVES[name](params["p"]).contiguous()
@@ -37,5 +37,22 @@ def test_rebuild_equals_fresh_build(name, seed):
         (r0, c0), (r1, c1) = scene.adjacency(), fresh.adjacency()
         assert torch.equal(r0, r1) and torch.equal(c0, c1)
         assert scene.info()["n_hidden"] == fresh.info()["n_hidden"]
+        fresh.destroy()
+    scene.destroy()
+
+
+@pytest.mark.parametrize("n", [23999, 24000, 24001])
+def test_sizes_where_empty_cells_start_to_be_taken_out(n):
+    import paper_2604_24994_amd as pf
+    print(f"case {n} cells, sites moved by 1e-3", flush=True)
+    params = pf.to_device_params(W.scene_uniform(n, seed=4))
+    scene = pf.build_scene(params)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    for _ in range(2):
+        params = dict(params, p=params["p"] + 1e-3 * torch.randn(n, 3, device="cuda", generator=g))
+        pf.update_scene(scene, params)
+        fresh = pf.build_scene(params)
+        (r0, c0), (r1, c1) = scene.adjacency(), fresh.adjacency()
+        assert torch.equal(r0, r1) and torch.equal(c0, c1)
         fresh.destroy()
     scene.destroy()
