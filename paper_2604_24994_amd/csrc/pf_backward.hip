@@ -336,36 +336,12 @@ __device__ inline int2 acc_slot(int t) {
 
 __device__ inline float softplus_b(float x) { return x > 20.0f ? x : log1pf(expf(x)); }
 
-// A wave-uniform double moved to scalar registers.
-__device__ inline double uni(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // 1/x in float64 (x != 0): the hardware reciprocal (about 24 bits on
 // gfx950) refined by one Newton step, about 47 bits: the chains below end
 // in float32.
 __device__ inline double rcp_d(double x) {
   const double r = __builtin_amdgcn_rcp(x);
   return fma(r, fma(-x, r, 1.0), r);
-}
-
-// Length and reciprocal length of a 2-vector from its squared length x2
-// (float64): the hardware reciprocal square root (about 24 bits) refined by
-// one Newton step, r <- r (3 - x2 r^2) / 2 (about 47 bits), then
-// |v| = x2 / |v|.  Both are 0 for x2 = 0.
-__device__ inline void len_rlen(double x2, double& len, double& rlen) {
-  if (x2 > 0.0) {
-    double r = __builtin_amdgcn_rsq(x2);
-    const double hx = 0.5 * x2;
-    r = r * fma(-hx * r, r, 1.5);
-    rlen = r;
-    len = x2 * r;
-  } else {
-    rlen = 0.0;
-    len = 0.0;
-  }
 }
 
 // Softmax backward of the soft-Voronoi weights at texture point u.  With

@@ -145,11 +145,6 @@ __device__ inline float4 live_ball(const float4* __restrict__ geo, const float* 
 // Thread-local error text.
 void set_error(const std::string& msg);
 
-// Device allocation helpers (stream-ordered); return false on failure with
-// the error text set.
-bool dmalloc(void** p, size_t bytes, hipStream_t s, const char* what);
-void dfree(void* p, hipStream_t s);
-
 // Library device memory: blocks cached by the library and reused
 // stream-ordered.  pool_alloc returns a block usable on stream s; pool_free
 // gives it back once the work queued on s so far has finished with it.

@@ -96,7 +96,6 @@ typedef const __attribute__((address_space(4))) float* ufloat_p;
 typedef const __attribute__((address_space(4))) vec4f* uvec4_p;
 __device__ inline ufloat_p uniform_ptr(const float* p) { return (ufloat_p)p; }
 __device__ inline uvec4_p uniform_ptr(const float4* p) { return (uvec4_p)p; }
-__device__ inline float4 load4(const float4* p) { return *p; }
 __device__ inline float4 load4(uvec4_p p) {
   const vec4f v = *p;
   return make_float4(v.x, v.y, v.z, v.w);
