@@ -394,14 +394,15 @@ __device__ inline void sv_backward(const float* site, double ux_d, double uy_d, 
 // Two waves per SIMD: at most 256 VGPRs, which the per-record float64
 // chain fills without spilling (at three waves, 168 VGPRs, it spilled and ran
 // 5% slower), and eight workgroups' LDS per CU.
-// The kernel is bound by the vector instructions it issues (77% of the SIMDs'
-// cycles) and, with two waves to hide them, by the waits between.  37.1 ms for
-// the 8 views of 1600x1066 of a training step at 1,048,576 cells became 31.3:
+// The kernel is bound by the vector instructions it issues (66% of the SIMDs'
+// cycles at 2.4 GHz) and, with two waves to hide them, by the waits between (20% of
+// the waves' cycles).  37.1 ms for the 8 views of 1600x1066 of a training step at
+// 1,048,576 cells became 31.4 to 31.9, run by run:
 // the sites' lobes and the transposed sums as 4x4x1 FP32 MFMAs, sums kept per
 // lane, choices instead of branches (together 37.1 -> 36.4, the waits having become the bound);
 // then planes, cameras, axes and colours in LDS, the face sums without LDS atomics
 // and 16-byte LDS reads (-> 32.3), the transposed products' initial values and a
-// pixel's row without an integer division (-> 31.3).
+// pixel's row without an integer division (-> 31.3 there).
 __global__ void __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) k_bwd_cell(
     const pf_camera* __restrict__ cams, int ncam, const int4* __restrict__ ri, const float4* __restrict__ rf,
     const int32_t* __restrict__ order, const int4* __restrict__ chunks, const float* __restrict__ prm_p,

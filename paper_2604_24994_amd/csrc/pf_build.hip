@@ -1,5 +1,5 @@
 // Scene build: face adjacency of the power diagram clipped to the domain
-// box, tight cull radii and hidden-cell flags.
+// box, a ball around each cell's dense part and hidden-cell flags.
 //
 // What is computed: for every cell i the faces of
 //   Pi_i = { x : |x-p_i|^2 - w_i <= |x-p_j|^2 - w_j }  (appendix B)
@@ -36,7 +36,7 @@ constexpr int SPL_BIG = 8;        // vertex slots per lane of the third pass
 // traversal stack: the unvisited siblings along one root-to-leaf path,
 // (levels - 2) x 63 + 64 + the root's children: 190 entries at 16M sites
 constexpr int STACK = 192;
-constexpr int WIT = 8;           // per empty cell: sites whose planes emptied it (seeds of the next build)
+constexpr int WIT = 8;           // per empty cell: four planes that prove it empty, then seeds (write_witness)
 constexpr int64_t ELIM_MIN = 24000;   // cells from which the empty ones are taken out first (build_scene_impl)
 constexpr int RING_K = 16;        // rank of the leaf mate that sets the first ring radius
 // Upper bound on candidate clips plus node visits per cell; a cell that

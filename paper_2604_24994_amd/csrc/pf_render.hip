@@ -1405,8 +1405,9 @@ constexpr int WALK_GROUP = 12;
 // texture, or, where few do, every ray's oldest contribution with per-lane reads.
 // What bounds it are the instructions it issues (84% of the SIMDs' cycles over 8
 // views of 1600x1066), a part of its lanes idle, and the waits for a step's dependent
-// loads (44% of its waves' cycles); the ring's LDS and the registers leave four
-// waves per SIMD.
+// loads (44% of its waves' cycles); the ring's LDS (40,960 bytes) and the registers
+// leave four waves per SIMD, two in the record-writing form (51,200 bytes, whose
+// three workgroups per CU the register allocation does not use).
 // 921600 rays through 1M cells (67 cells, 18 faces each, 22 contributions per
 // ray): 8.9 ms with two face passes and the radiance in place, 5.7 ms with one,
 // 3.7 ms with the radiance deferred (1.9 ms of it the faces, 0.6 the opacity);

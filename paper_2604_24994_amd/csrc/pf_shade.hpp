@@ -1,9 +1,11 @@
 // Per-(ray, cell) device math shared by the rasteriser, the ray walk and the
 // backward pass, so that the two renderers evaluate every contribution's
-// geometry with the same instructions (the radiance's lobe softmaxes are
-// taken without the max shift in the rasteriser and with it in the walk,
-// which holds the texture per lane in fewer registers; the two agree up to
-// rounding).
+// geometry with the same arithmetic.  One product differs: the slope of the last
+// raster face where their number is odd (piece_geometry), by which opacities
+// differ in the last bits at 0.1% of the pixels.  Colours agree up to rounding: a
+// wave that shades one cell, always in the rasteriser and mostly in the walk, takes
+// the lobe softmaxes without the max shift (radiance_wave), a ray by itself with it
+// (radiance_lane).
 //
 // Numerics: the ray is generated in float64 and, per cell, re-expressed in
 // the cell's local frame in float64: q = closest-approach offset from p_i,
@@ -408,7 +410,11 @@ __device__ inline Piece piece_geometry(const RayD& R, const Local& L, float r, V
     f = fn;
     more = f + 2 <= nfaces && __any(I.s0 < I.s1);
   }
-  if (f + 1 == nfaces) {   // (its slope rounded as the other products here, not as face_slope)
+  if (f + 1 == nfaces) {
+    // (its slope rounded as the other products here.  With face_slope, raster and
+    // walk have the same opacities bit for bit, but other rays graze such a face,
+    // and the gradient of power moved by 2e-5 of its norm in one training step of
+    // eight: too far for what it gives.)
     const float4 pl = load4(faces + __builtin_amdgcn_readfirstlane(f));
     clip(pl, dot3(R.fx, R.fy, R.fz, pl.x, pl.y, pl.z) + 0.0f, f);
   }
@@ -469,9 +475,9 @@ __device__ inline vec4f wave_lobes(const WaveTex& W, float gx, float gy, float g
 static_assert(KD == 8 && MA == 8, "wave_tex and wave_lobes: 64 site-axis pairs, two colour blocks of eight");
 
 // Radiance at texture point u for direction d: base colour plus the
-// soft-Voronoi blend of the detail sites' Spherical-Voronoi colours, for the
-// rasteriser (one cell per wave; all lanes take part, those outside `on` get
-// an unspecified colour).  The lobes are exponentiated in base 2 without the
+// soft-Voronoi blend of the detail sites' Spherical-Voronoi colours, for a wave
+// that shades one cell (all lanes take part, those outside `on` get an
+// unspecified colour).  The lobes are exponentiated in base 2 without the
 // max shift; where a site's sum leaves [2^-100, 2^100], the colour is evaluated
 // again with each site's logits shifted by their largest (as in
 // softmax2_sum).  That rare pass runs over the sites in a loop that is not
@@ -531,10 +537,10 @@ __device__ inline void radiance_wave(const float* __restrict__ tex, FP tx, FP rg
   }
 }
 
-// The same with a cell per lane, the texture read per lane (the walk, where few
-// rays of the wave share a cell): every softmax shifted by its largest logit,
-// which keeps fewer values live than the unshifted form with its rare shifted
-// pass.
+// The same with a cell per lane, the texture read per lane (the walk, where too
+// few rays of the wave hold the cell at once): every softmax shifted by its
+// largest logit, which keeps fewer values live than the unshifted form with its
+// rare shifted pass.
 __device__ inline void radiance_lane(const float* __restrict__ tx, const float* __restrict__ rgb, float ux, float uy,
                                      float fx, float fy, float fz, float tau, float& cr, float& cg, float& cb) {
   float w[KD];
