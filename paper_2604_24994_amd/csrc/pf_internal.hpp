@@ -27,6 +27,7 @@ constexpr int FLAG_OVER_VERTS = 4;    //   vertex slots
 constexpr int FLAG_OVER_PLANES = 8;   //   live planes
 constexpr int FLAG_OVER_WORK = 16;    //   work limit
 constexpr int FLAG_OVER_STACK = 32;   //   traversal stack
+constexpr int FLAG_SAME_PLACE = 64;   // (with EMPTY_POWER) a site at the same place owns it
 
 // Implicit 64-ary tree over the Morton-sorted sites: level 0 = sites,
 // level L >= 1 = nodes (box of their sites; lo.w = largest weight, hi.w =
