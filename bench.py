@@ -49,18 +49,18 @@ FLOPS_BWD_PER_CONTRIB = 5100
 # (FETCH_SIZE reads 0.5 GiB: x2.0; WRITE_SIZE reads 1 GiB: x1.0).  Valid only
 # for the kernel sources with these hashes; otherwise the bench reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-_SRC_SHADE = {"pf_shade.hpp": "c6d4fcd5f9860659", "pf_internal.hpp": "a6431073dbb93ac5",
+_SRC_SHADE = {"pf_shade.hpp": "c6d4fcd5f9860659", "pf_internal.hpp": "587e70c4d31060c6",
               "pf_record.hpp": "d8db4e8267ff8479"}
 TRAFFIC = {
-    "k_bwd_cell": {"fetch_kib": 7794446.5, "write_kib": 2254476.7,
-                   "sources": {"pf_backward.hip": "d01f1cc8aa69108d", **_SRC_SHADE}},
+    "k_bwd_cell": {"fetch_kib": 7794448.6, "write_kib": 2254680.4,
+                   "sources": {"pf_backward.hip": "eb6dc472a67aacd9", **_SRC_SHADE}},
     # (k_raster and k_raster_split together)
-    "k_raster_store": {"fetch_kib": 17345684.0, "write_kib": 12167597.7,
+    "k_raster_store": {"fetch_kib": 17321397.9, "write_kib": 12167377.6,
                        "sources": {"pf_render.hip": "fdca6d01d836118d", **_SRC_SHADE}},
-    "k_trace": {"fetch_kib": 4883796.3, "write_kib": 26650.0,
+    "k_trace": {"fetch_kib": 4880084.1, "write_kib": 26650.0,
                 "sources": {"pf_render.hip": "fdca6d01d836118d", **_SRC_SHADE}},
-    "k_clip": {"fetch_kib": 481944.6, "write_kib": 183585.4,
-               "sources": {"pf_build.hip": "a8aca21dc2a5000e", "pf_internal.hpp": "a6431073dbb93ac5",
+    "k_clip": {"fetch_kib": 481866.1, "write_kib": 183585.4,
+               "sources": {"pf_build.hip": "2a7f53803a3372f8", "pf_internal.hpp": "587e70c4d31060c6",
                            "pf_record.hpp": "d8db4e8267ff8479"}},
 }
 

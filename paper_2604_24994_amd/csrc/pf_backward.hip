@@ -394,10 +394,10 @@ __device__ inline void sv_backward(const float* site, double ux_d, double uy_d, 
 // Two waves per SIMD: at most 256 VGPRs, which the per-record float64
 // chain fills without spilling (at three waves, 168 VGPRs, it spilled and ran
 // 5% slower), and eight workgroups' LDS per CU.
-// The kernel is bound by the vector instructions it issues (66% of the SIMDs'
+// The kernel is bound by the vector instructions it issues (65% of the SIMDs'
 // cycles at 2.4 GHz) and, with two waves to hide them, by the waits between (20% of
 // the waves' cycles).  37.1 ms for the 8 views of 1600x1066 of a training step at
-// 1,048,576 cells became 31.4 to 31.9, run by run:
+// 1,048,576 cells became 31.2 to 32.2, run by run:
 // the sites' lobes and the transposed sums as 4x4x1 FP32 MFMAs, sums kept per
 // lane, choices instead of branches (together 37.1 -> 36.4, the waits having become the bound);
 // then planes, cameras, axes and colours in LDS, the face sums without LDS atomics
