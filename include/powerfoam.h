@@ -175,6 +175,8 @@ typedef struct {
    the largest displacement it was built with bounds that cell by all of it,
    which costs time, not pixels.  params (host) is copied; its arrays are referenced.
    opts (host) may be NULL.  Synchronises the stream (sizes the adjacency).
+   Of several sites at one place the heaviest owns it (of equal weights the one of
+   lowest index); the others' cells are empty and no face leads to them.
    A cell of zero density (occ_logit = -inf, e.g. a Steiner cell) whose power
    cell exceeds the face capacity (256 planes) is dropped: the build is
    repeated as if it were absent (it can never contribute to an image; the
